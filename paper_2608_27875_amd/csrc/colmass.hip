@@ -77,9 +77,15 @@ __device__ __forceinline__ void stage_rows_store(uint8_t* buf, const v4u (&r)[2]
 // log2 domain.
 __global__ void __launch_bounds__(kCmThreads)
 colmass_lse_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-                   float* __restrict__ part, CmGeom gm) {
+                   float* __restrict__ part, uint32_t* __restrict__ hist,
+                   uint32_t* __restrict__ tws, size_t tws_words, CmGeom gm) {
   __shared__ __attribute__((aligned(16))) uint8_t kbuf[2][kStageBytes];
   const int bj = blockIdx.y;
+  if (blockIdx.x == 0) {   // this head's key histogram and candidate count, filled later
+    for (int i = threadIdx.x; i < kSelHistBins; i += kCmThreads)
+      hist[(size_t)bj * kSelHistBins + i] = 0u;
+    if (threadIdx.x == 0) tws[(size_t)bj * tws_words] = 0u;
+  }
   const int grp = blockIdx.x / gm.ks, split = blockIdx.x % gm.ks;
   const int b = bj / gm.Hkv, j = bj % gm.Hkv;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -185,9 +191,12 @@ colmass_merge_kernel(const float* __restrict__ part, float* __restrict__ lse, Cm
 // queries; the 32 query lanes are summed at the end.
 __global__ void __launch_bounds__(kCmThreads)
 colmass_sum_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-                   const float* __restrict__ lse, float* __restrict__ S, CmGeom gm) {
+                   const float* __restrict__ lse, float* __restrict__ S,
+                   uint32_t* __restrict__ hist, CmGeom gm) {
   __shared__ __attribute__((aligned(16))) uint8_t qbuf[2][kStageBytes];
   __shared__ float lbuf[2][kStageRows];
+  __shared__ uint32_t keys[kSelHistBins];   // key histogram of the workgroup's scores
+  hist_clear(keys);
   const int bj = blockIdx.y;
   const int b = bj / gm.Hkv, j = bj % gm.Hkv;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -264,8 +273,13 @@ colmass_sum_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
 #pragma unroll
       for (int o = 16; o >= 1; o >>= 1) v += __shfl_xor(v, o, 32);
       const int key = key0 + h * 32 + (e >> 2) * 8 + lh * 4 + (e & 3);
-      if (col == 0 && key < gm.P) S[(size_t)bj * gm.P + key] = v;
+      if (col == 0 && key < gm.P) {
+        S[(size_t)bj * gm.P + key] = v;
+        atomicAdd(&keys[order_key(v) >> kHistShift], 1u);
+      }
     }
+  __syncthreads();
+  hist_flush(keys, hist + (size_t)bj * kSelHistBins);
 }
 
 }  // namespace
@@ -278,7 +292,8 @@ size_t colmass_ws_bytes(const hyq_shape& s) {
 }
 
 hipError_t launch_colmass_scores(const hyq_shape& s, const hyq_sizes& z, const uint16_t* Q,
-                                 const uint16_t* K, float* scores, float* ws, hipStream_t st) {
+                                 const uint16_t* K, float* scores, uint32_t* hist, uint32_t* tws,
+                                 size_t tws_words, float* ws, hipStream_t st) {
   CmGeom gm;
   gm.Hq = s.Hq;
   gm.Hkv = s.Hkv;
@@ -294,10 +309,11 @@ hipError_t launch_colmass_scores(const hyq_shape& s, const hyq_sizes& z, const u
   float* part = ws;
   float* lse = ws + (size_t)BH * nq * 2 * kCmSplits;
   const int ngrp = (gm.g * gm.ntr + kCmWaves - 1) / kCmWaves;
-  colmass_lse_kernel<<<dim3(ngrp * gm.ks, BH), kCmThreads, 0, st>>>(Q, K, part, gm);
+  colmass_lse_kernel<<<dim3(ngrp * gm.ks, BH), kCmThreads, 0, st>>>(Q, K, part, hist, tws, tws_words,
+                                                                     gm);
   colmass_merge_kernel<<<dim3((nq + 255) / 256, BH), 256, 0, st>>>(part, lse, gm);
   colmass_sum_kernel<<<dim3((z.P + kCmWaves * 64 - 1) / (kCmWaves * 64), BH), kCmThreads, 0, st>>>(
-      Q, K, lse, scores, gm);
+      Q, K, lse, scores, hist, gm);
   return hipGetLastError();
 }
 

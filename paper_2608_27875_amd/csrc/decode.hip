@@ -1,4 +1,4 @@
-// Decode path of HyQuant (Section 4.3): Freeze (Algorithm 4, App. A.4), the
+// Decode path of HyQuant (Section 4.3) after Freeze (quantize.hip): the
 // staging buffer and its merges into the quantized prefix, and the decode
 // attention of Algorithm 3 (App. A.3): the quantized prefix split along the
 // sequence axis, every split an online softmax, the splits and the
@@ -51,61 +51,6 @@ constexpr int kPartStride = kDecodePartFloats;
 constexpr float kLazyD = 8.0f;             // rescale only when the max grows by > 2^8
 constexpr float kMinusBigD = -1.0e30f;
 constexpr int kMaxGroup = 8;
-
-// ---------------------------------------------------------------------------
-// Freeze: gather the vertical-line rows and the window into the bf16 rows of
-// the cache (K row-major, V channel-major); every other row is zeroed.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-freeze_gather_kernel(const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
-                     const int32_t* __restrict__ idx, uint16_t* __restrict__ fk,
-                     uint16_t* __restrict__ fv, int N, int W, int k, int vl_rows, int nfp) {
-  __shared__ uint16_t tile[kBlock][kHeadDim + 2];
-  const int bj = blockIdx.y;
-  const int row = threadIdx.x >> 2, c0 = (threadIdx.x & 3) * 32;
-  const int i = blockIdx.x * kBlock + row;
-  int src = -1;
-  if (i < k) src = idx[(size_t)bj * k + i];
-  else if (i >= vl_rows && i - vl_rows < W) src = N - W + (i - vl_rows);
-  v4u kw[4], vw[4];
-  if (src >= 0) {
-    const v4u* kp = reinterpret_cast<const v4u*>(K + ((size_t)bj * N + src) * kHeadDim + c0);
-    const v4u* vp = reinterpret_cast<const v4u*>(V + ((size_t)bj * N + src) * kHeadDim + c0);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      kw[u] = kp[u];
-      vw[u] = vp[u];
-    }
-  } else {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) kw[u] = vw[u] = v4u{0u, 0u, 0u, 0u};
-  }
-  v4u* kd = reinterpret_cast<v4u*>(fk + ((size_t)bj * nfp + i) * kHeadDim + c0);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) kd[u] = kw[u];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      tile[row][c0 + u * 8 + 2 * e] = (uint16_t)(vw[u][e] & 0xffffu);
-      tile[row][c0 + u * 8 + 2 * e + 1] = (uint16_t)(vw[u][e] >> 16);
-    }
-  }
-  __syncthreads();
-  // transposed write: thread -> (channel d, 32 rows)
-  const int d = threadIdx.x >> 1, r0 = (threadIdx.x & 1) * 32;
-  v4u o[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      o[u][e] = (uint32_t)tile[r0 + u * 8 + 2 * e][d] |
-                ((uint32_t)tile[r0 + u * 8 + 2 * e + 1][d] << 16);
-  v4u* vd = reinterpret_cast<v4u*>(fv + ((size_t)bj * kHeadDim + d) * nfp +
-                                   (size_t)blockIdx.x * kBlock + r0);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) vd[u] = o[u];
-}
 
 // ---------------------------------------------------------------------------
 // Append one token (and, first, merge the W_s oldest window tokens into W_s/64
@@ -867,16 +812,6 @@ size_t decode_ws_bytes(const hyq_dcache& c) {
   const int64_t S = (c.cap_blocks + 2 * kDecWaves - 1) / (2 * kDecWaves) +
                     (nft + kDecWaves - 1) / kDecWaves;
   return (size_t)c.B * c.Hkv * S * (c.Hq / c.Hkv) * kPartStride * sizeof(float);
-}
-
-hipError_t launch_freeze_gather(const hyq_dcache& c, int N, const uint16_t* K, const uint16_t* V,
-                                hipStream_t st) {
-  const int nfp = c.vl_rows + c.ring_rows;
-  dim3 grid(nfp / kBlock, c.B * c.Hkv);
-  freeze_gather_kernel<<<grid, 256, 0, st>>>(K, V, c.vl_pos, static_cast<uint16_t*>(c.fp_k),
-                                             static_cast<uint16_t*>(c.fp_v), N, c.window, c.n_vl,
-                                             c.vl_rows, nfp);
-  return hipGetLastError();
 }
 
 hipError_t launch_decode_append(const hyq_dcache& c, const uint16_t* k_new, const uint16_t* v_new,

@@ -327,7 +327,8 @@ HYQ_API int hyq_select_vertical(const hyq_shape* shape, const void* Q, const voi
   const SelectWs w = select_ws(*shape, z, ws, scores);
   return hip_status(hyq::launch_select(*shape, z, static_cast<const uint16_t*>(Q),
                                        static_cast<const uint16_t*>(K), idx, w.scores, w.qsum,
-                                       w.hist, w.tws, w.cm, static_cast<hipStream_t>(stream)),
+                                       w.hist, w.tws, w.cm, nullptr,
+                                       static_cast<hipStream_t>(stream)),
                     "hyq_select_vertical launch");
 }
 
@@ -385,10 +386,25 @@ HYQ_API int hyq_prefill(const hyq_shape* shape, const void* Q, const void* K, co
   if ((rc = check_attn_args(shape, z, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes,
                             v_scale, kq_pos, softmax_scale, out, out_dtype)))
     return rc;
-  if ((rc = hyq_select_vertical(shape, Q, K, idx, nullptr, ws, ws_bytes, stream))) return rc;
-  if ((rc = hyq_quantize(shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes,
-                         v_scale, kq_pos, stream)))
-    return rc;
+  if (z.k > 0 && shape->bits_kv != 16) {
+    // the selection's launches carry the Q blocks; then the K/V blocks
+    const hyq_shape& s = *shape;
+    const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const SelectWs w = select_ws(s, z, ws, nullptr);
+    const hyq::QuantQ qq = hyq::quant_q_all(s, z, q, q_codes, q_scale);
+    const hipError_t e = hyq::launch_select(s, z, q, k, idx, w.scores, w.qsum, w.hist, w.tws, w.cm,
+                                            &qq, st);
+    if (e != hipSuccess) return hip_status(e, "hyq_prefill selection launch");
+    hyq::launch_quant_kv(s, z, k, static_cast<const uint16_t*>(V), idx, kq_pos,
+                         static_cast<uint8_t*>(k_codes), k_scale, static_cast<uint8_t*>(v_codes),
+                         v_scale, st);
+  } else {
+    if ((rc = hyq_select_vertical(shape, Q, K, idx, nullptr, ws, ws_bytes, stream))) return rc;
+    if ((rc = hyq_quantize(shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes,
+                           v_scale, kq_pos, stream)))
+      return rc;
+  }
   return hyq_attn_prefill(shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes,
                           v_scale, kq_pos, softmax_scale, out, out_dtype, stream);
 }
@@ -427,26 +443,16 @@ HYQ_API int hyq_freeze(const hyq_shape* prefill, const void* Q, const void* K, c
     return fail(HYQ_EINVAL, "workspace too small: %zu bytes given, %zu needed", ws_bytes,
                 rz.freeze_ws_bytes);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int BHkv = prefill->B * prefill->Hkv;
   if (z.k > 0) {
     const SelectWs w = select_ws(*prefill, z, ws, nullptr);
     hipError_t e = hyq::launch_select(*prefill, z, static_cast<const uint16_t*>(Q),
                                       static_cast<const uint16_t*>(K), cache->vl_pos, w.scores,
-                                      w.qsum, w.hist, w.tws, w.cm, st);
+                                      w.qsum, w.hist, w.tws, w.cm, nullptr, st);
     if (e != hipSuccess) return hip_status(e, "hyq_freeze selection launch");
   }
-  if (cache->cap_blocks > 0) {
-    hyq::launch_compact(cache->vl_pos, cache->q_pos, z.k, z.P, z.nQ, cache->cap_blocks * 64,
-                        BHkv, st);
-    hyq::launch_quant_kv(prefill->bits_kv, prefill->kv_format, static_cast<const uint16_t*>(K),
-                         static_cast<const uint16_t*>(V), cache->q_pos,
-                         static_cast<uint8_t*>(cache->k_codes), cache->k_scale,
-                         static_cast<uint8_t*>(cache->v_codes), cache->v_scale, prefill->L, z.nQ,
-                         z.n_kvblk, cache->cap_blocks, BHkv, st);
-  }
-  const hipError_t e = hyq::launch_freeze_gather(*cache, prefill->L,
-                                                 static_cast<const uint16_t*>(K),
-                                                 static_cast<const uint16_t*>(V), st);
+  const hipError_t e = hyq::launch_freeze_kv(*cache, z, prefill->L,
+                                             static_cast<const uint16_t*>(K),
+                                             static_cast<const uint16_t*>(V), st);
   if (e != hipSuccess) return hip_status(e, "hyq_freeze launch");
   cache->n_merged = 0;
   cache->ring_head = 0;

@@ -17,30 +17,31 @@
 //   - while the scores are produced, every workgroup counts its keys by
 //     their top 12 bits in LDS and adds the non-empty bins to a histogram of
 //     its KV head in the workspace;
-//   - the classification kernel (1024 keys per workgroup) finds the bin
-//     holding the k-th largest key from that histogram, writes a bitmap of
-//     the positions in higher bins and appends the keys of that bin (about
-//     1% of them) to a candidate list;
-//   - one workgroup per KV head resolves the remaining 20 bits of the
-//     threshold with two 10-bit radix passes over the candidates, then
-//     writes the chosen positions in ascending order (ordered compaction of
-//     the bitmaps; keys equal to the threshold lowest position first).
-// The per-key work runs on many workgroups; the one workgroup per head
-// touches only the candidates and one bitmap word per 32 positions.
+//   - classification: the bin holding the k-th largest key comes from that
+//     histogram; a bitmap takes the positions in higher bins, a candidate
+//     list the keys of that bin (about 1% of them);
+//   - two 10-bit radix passes over the candidates resolve the remaining 20
+//     bits of the threshold; the chosen positions are written in ascending
+//     order (ordered compaction of the bitmaps; keys equal to the threshold
+//     lowest position first).
+// Up to kWholeKeys keys per head, one workgroup per head does all of that in
+// one launch (topk_kernel); longer prefixes classify on many workgroups first
+// (topk_classify_kernel, topk_final_kernel).
+//
+// A prefill's Q quantization needs nothing of the selection: its blocks ride
+// along as extra workgroups of the tail-proxy launch, which alone is bound by
+// latency (32k: 7.7 us, and 76 us for Q in a launch of its own; 65 us
+// together).  Giving the top-k launch a share as well was slower: its 1024
+// threads and 50 KB of LDS leave one quantizing workgroup per CU, whose waves
+// all load and then all compute (8k prefill 522 us with every block here, 545
+// / 550 / 576 with a quarter / half / all of them there).
 #include "hyq_internal.h"
+#include "quant_dev.h"
 
 #pragma clang fp contract(off)
 
 namespace hyq {
 namespace {
-
-constexpr int kHistShift = 32 - kSelHistBits;   // the histogram bin is key >> kHistShift
-
-// Order-preserving map float -> uint32 (larger float, larger key); -0 -> +0.
-__device__ __forceinline__ uint32_t order_key(float f) {
-  uint32_t u = __float_as_uint(f + 0.0f);   // -0 + 0 = +0
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
 
 // Per-head top-k scratch in the workspace: a 4-word header (the candidate
 // count, then the bin of the k-th largest key and the keys still to take in
@@ -75,14 +76,19 @@ __device__ __forceinline__ TopkWs topk_ws(uint32_t* base, int bj, int P) {
 constexpr int kTailRows = 256;
 constexpr int kTailThreads = kTailRows;
 constexpr int kTailCh = 16;   // channels per workgroup
+// Workgroups from n_tail on quantize one Q block each instead.
+template <int QFMT>
 __global__ void __launch_bounds__(kTailThreads)
 tail_proxy_kernel(const uint16_t* __restrict__ Q, float* __restrict__ qpart,
-                  uint32_t* __restrict__ hist, uint32_t* __restrict__ tws, int Hq, int Hkv, int L,
-                  int t, int P) {
+                  uint32_t* __restrict__ hist, uint32_t* __restrict__ tws, int BHq, int g, int L,
+                  int t, int P, int n_tail, QuantQ qq) {
   __shared__ uint4 rows[kTailRows][kTailCh / 8];
-  const int g = Hq / Hkv;
-  const int bh = blockIdx.x, c0 = blockIdx.y * kTailCh;
-  if (bh % g == 0 && blockIdx.y == 0) {
+  if ((int)blockIdx.x >= n_tail) {
+    quant_q_block<QFMT>(qq, (int)blockIdx.x - n_tail, reinterpret_cast<float*>(&rows[0][0]));
+    return;
+  }
+  const int bh = (int)blockIdx.x % BHq, cg = (int)blockIdx.x / BHq, c0 = cg * kTailCh;
+  if (bh % g == 0 && cg == 0) {
     uint32_t* hj = hist + (size_t)(bh / g) * kSelHistBins;
     for (int i = threadIdx.x; i < kSelHistBins; i += kTailThreads) hj[i] = 0u;
     if (threadIdx.x < 4) tws[(size_t)(bh / g) * topk_ws_words(P) + threadIdx.x] = 0u;
@@ -115,21 +121,8 @@ tail_proxy_kernel(const uint16_t* __restrict__ Q, float* __restrict__ qpart,
   if (d < kTailCh) qpart[(size_t)bh * kHeadDim + c0 + d] = a;
 }
 
-// Workgroup-local key histogram (top kSelHistBits bits of the order key),
-// flushed into the KV head's histogram in global memory.
-constexpr int kHistThreads = 1024;         // hist_kernel: one key per thread
 constexpr int kScoreThreads = 512;         // score_kernel: 64 keys per wave
 constexpr int kScoreRows = kScoreThreads;  // keys per score workgroup
-
-__device__ __forceinline__ void hist_clear(uint32_t* lh) {
-  for (int i = threadIdx.x; i < kSelHistBins; i += blockDim.x) lh[i] = 0u;
-}
-__device__ __forceinline__ void hist_flush(const uint32_t* lh, uint32_t* __restrict__ gh) {
-  for (int i = threadIdx.x; i < kSelHistBins; i += blockDim.x) {
-    const uint32_t c = lh[i];
-    if (c) atomicAdd(gh + i, c);
-  }
-}
 
 // Lane exchange within groups of four lanes (DPP quad permutations).
 __device__ __forceinline__ float xor1(float x) {
@@ -236,28 +229,6 @@ score_kernel(const uint16_t* __restrict__ K, const float* __restrict__ qpart,
   hist_flush(lh, hist + (size_t)bj * kSelHistBins);
 }
 
-// Clears the key histogram and the top-k candidate count of each head (one
-// workgroup per head; the tail-proxy kernel does this on the other path).
-__global__ void hist_zero_kernel(uint32_t* __restrict__ hist, uint32_t* __restrict__ tws, int P) {
-  const int bj = blockIdx.x;
-  for (int i = threadIdx.x; i < kSelHistBins; i += blockDim.x)
-    hist[(size_t)bj * kSelHistBins + i] = 0u;
-  if (threadIdx.x == 0) tws[(size_t)bj * topk_ws_words(P)] = 0u;
-}
-
-// Key histogram of scores computed elsewhere (the column-mass selector).
-__global__ void __launch_bounds__(kHistThreads)
-hist_kernel(const float* __restrict__ S, uint32_t* __restrict__ hist, int P) {
-  __shared__ uint32_t lh[kSelHistBins];
-  const int bj = blockIdx.x;
-  hist_clear(lh);
-  __syncthreads();
-  const int p = blockIdx.y * kHistThreads + threadIdx.x;
-  if (p < P) atomicAdd(&lh[order_key(S[(size_t)bj * P + p]) >> kHistShift], 1u);
-  __syncthreads();
-  hist_flush(lh, hist + (size_t)bj * kSelHistBins);
-}
-
 constexpr int kTopkThreads = 1024;
 constexpr int kTopkWaves = kTopkThreads / 64;
 constexpr int kDigitBits = 10;
@@ -268,64 +239,59 @@ static_assert(kDigitBins == kTopkThreads, "one digit bin per thread");
 
 struct TopkShared {
   uint32_t dig[kDigitBins];
-  uint32_t wtot[kTopkWaves];
+  uint32_t wtot[2][kTopkWaves];   // wave totals of a block scan (scans alternate)
   uint32_t sel_bin;
   int sel_rem;
 };
 
-// Inclusive suffix sum over the workgroup's threads in thread order: the
-// sum of x over this thread and every later one.
-__device__ __forceinline__ uint32_t block_suffix(uint32_t x, TopkShared& sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t s = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_down(s, o, 64);
-    if (lane + o < 64) s += y;
-  }
-  if (lane == 0) sh.wtot[w] = s;
-  __syncthreads();
-  uint32_t later = 0;
-  for (int v = w + 1; v < kTopkWaves; ++v) later += sh.wtot[v];
-  __syncthreads();
-  return s + later;
+// Inclusive prefix sum over the 16 lanes of a DPP row, and over the wave.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t x) {   // lanes without a source add 0
+  return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t row_prefix(uint32_t x) {
+  x = dpp_add<0x111, 0xF>(x);   // row_shr:1, 2, 4, 8
+  x = dpp_add<0x112, 0xF>(x);
+  x = dpp_add<0x114, 0xF>(x);
+  return dpp_add<0x118, 0xF>(x);
+}
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+  x = row_prefix(x);
+  x = dpp_add<0x142, 0xA>(x);      // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xC>(x);   // row_bcast:31 into rows 2 and 3
 }
 
-// Exclusive prefix sum over the workgroup's threads in thread order; the
-// sum over all threads goes to `total`.
-__device__ __forceinline__ uint32_t block_prefix_excl(uint32_t x, TopkShared& sh,
+// Exclusive prefix sum over the workgroup's threads in thread order; the sum
+// over all threads goes to `total`.  One barrier: a scan writes the wave
+// totals the last one did not (slot alternates from call to call), so they
+// are overwritten only after another scan's barrier.
+__device__ __forceinline__ uint32_t block_prefix_excl(uint32_t x, TopkShared& sh, int slot,
                                                       uint32_t& total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t s = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(s, o, 64);
-    if (lane >= o) s += y;
-  }
-  if (lane == 63) sh.wtot[w] = s;
+  static_assert(kTopkWaves == 16, "the wave totals fill one DPP row");
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const uint32_t incl = wave_prefix(x);
+  if (lane == 63) sh.wtot[slot][w] = incl;
   __syncthreads();
-  uint32_t before = 0, all = 0;
-  for (int v = 0; v < kTopkWaves; ++v) {
-    const uint32_t t = sh.wtot[v];
-    before += v < w ? t : 0u;
-    all += t;
-  }
-  __syncthreads();
-  total = all;
-  return before + s - x;
+  const uint32_t t = row_prefix(sh.wtot[slot][lane & 15]);
+  total = (uint32_t)__builtin_amdgcn_readlane((int)t, 15);
+  const uint32_t before = w ? (uint32_t)__builtin_amdgcn_readlane((int)t, w - 1) : 0u;
+  return before + incl - x;
 }
 
-// Thread t owns the n bins c[0..n) = bins n*t .. n*t+n-1 of an ascending
+// Thread t owns the N bins c[0..N) = bins N*t .. N*t+N-1 of an ascending
 // histogram.  Finds the bin holding the need-th largest key and how many
 // keys of that bin are still to take; the owning thread publishes both.
 template <int N>
-__device__ __forceinline__ void find_bin(const uint32_t (&c)[N], int need, TopkShared& sh) {
+__device__ __forceinline__ void find_bin(const uint32_t (&c)[N], int need, TopkShared& sh,
+                                         int slot) {
   uint32_t mine = 0;
 #pragma unroll
   for (int e = 0; e < N; ++e) mine += c[e];
-  const uint32_t suf = block_suffix(mine, sh);
-  const uint32_t above = suf - mine;   // keys in the bins of later threads
-  if (above < (uint32_t)need && (uint32_t)need <= suf) {
+  uint32_t total;
+  const uint32_t before = block_prefix_excl(mine, sh, slot, total);
+  const uint32_t above = total - before - mine;   // keys in the bins of later threads
+  if (above < (uint32_t)need && (uint32_t)need <= above + mine) {
     uint32_t acc = above;
 #pragma unroll
     for (int e = N - 1; e >= 0; --e) {
@@ -345,7 +311,7 @@ __device__ __forceinline__ void hist_bin(const uint32_t* __restrict__ hist, int 
                                          TopkShared& sh) {
   const uint4 h4 = reinterpret_cast<const uint4*>(hist + (size_t)bj * kSelHistBins)[threadIdx.x];
   const uint32_t hc[4] = {h4.x, h4.y, h4.z, h4.w};
-  find_bin<4>(hc, k, sh);
+  find_bin<4>(hc, k, sh, 0);
 }
 
 // Classification, 1024 keys per workgroup (grid: head fastest, then key
@@ -386,29 +352,172 @@ topk_classify_kernel(const float* __restrict__ S, const uint32_t* __restrict__ h
   }
 }
 
+// The candidates of a head are kept as lists of which each wave owns one: the
+// first kLdsCap entries in LDS, the rest (crowded or tied bins) in the
+// workspace.  A wave appends to and reads only its own list.
+constexpr int kLdsCap = 128;
+struct Cands {
+  uint2* lds;
+  uint2* ws;
+  int n;
+};
+__device__ __forceinline__ uint2 cand_at(const Cands& cs, int c) {
+  return c < kLdsCap ? cs.lds[c] : cs.ws[c];
+}
+
 // Radix pass over the candidates whose bits above `shift + kDigitBits`
 // equal `prefix`: histogram of the next 10-bit digit, then the digit holding
 // the need-th largest of them.
-__device__ __forceinline__ void cand_digit_pass(const uint2* cand, int nc, uint32_t prefix,
-                                                int shift, int need, TopkShared& sh) {
+__device__ __forceinline__ void cand_digit_pass(const Cands& cs, uint32_t prefix, int shift,
+                                                int need, TopkShared& sh, int slot) {
   sh.dig[threadIdx.x] = 0u;
   __syncthreads();
   const int top = shift + kDigitBits;
-  for (int c = threadIdx.x; c < nc; c += kTopkThreads) {
-    const uint32_t key = cand[c].x;
+  for (int c = threadIdx.x & 63; c < cs.n; c += 64) {
+    const uint32_t key = cand_at(cs, c).x;
     if ((key >> top) == prefix) atomicAdd(&sh.dig[(key >> shift) & (kDigitBins - 1)], 1u);
   }
   __syncthreads();
   const uint32_t c1[1] = {sh.dig[threadIdx.x]};
-  __syncthreads();
-  find_bin<1>(c1, need, sh);
+  find_bin<1>(c1, need, sh, slot);
 }
 
-// Final top-k, one workgroup per (b, j):
+// The threshold key T from the candidates of bin `bin`, and how many keys
+// equal to T to take (lowest positions first).
+__device__ __forceinline__ uint32_t cand_threshold(const Cands& cs, uint32_t bin, int need,
+                                                   TopkShared& sh, int& need_eq) {
+  cand_digit_pass(cs, bin, kDigitBits, need, sh, 1);
+  const uint32_t d1 = sh.sel_bin;
+  cand_digit_pass(cs, (bin << kDigitBits) | d1, 0, sh.sel_rem, sh, 0);
+  need_eq = sh.sel_rem;
+  return (bin << (2 * kDigitBits)) | (d1 << kDigitBits) | sh.sel_bin;
+}
+
+// Chosen positions of kTopkThreads bitmap words, one per thread: every
+// position of `g` plus the lowest positions of `e` while need_eq lasts,
+// written ascending from out[o_base] on.  Advances o_base and eq_base.
+__device__ __forceinline__ void emit_words(uint32_t g, uint32_t e, int x, int need_eq, int k,
+                                           int32_t* __restrict__ out, uint32_t& o_base,
+                                           uint32_t& eq_base, TopkShared& sh) {
+  const int ne = __popc(e);
+  uint32_t eq_tot;
+  const int eq_before = (int)(eq_base + block_prefix_excl((uint32_t)ne, sh, 1, eq_tot));
+  int keep = max(0, min(ne, need_eq - eq_before));
+  uint32_t kept = 0;
+  for (; keep > 0; --keep) {   // the lowest `keep` positions equal to T
+    const uint32_t low = e & (0u - e);
+    kept |= low;
+    e ^= low;
+  }
+  uint32_t sel = g | kept, sel_tot;
+  uint32_t o = o_base + block_prefix_excl((uint32_t)__popc(sel), sh, 0, sel_tot);
+  while (sel) {
+    const int b = __builtin_ctz(sel);
+    if (o < (uint32_t)k) out[o] = x * 32 + b;   // never more than k
+    ++o;
+    sel &= sel - 1u;
+  }
+  o_base += sel_tot;
+  eq_base += eq_tot;
+}
+
+constexpr int kMapWords = 4096;                // bitmap words held in LDS (131072 positions)
+constexpr int kWholeKeys = kMapWords * 32;     // longest prefix of topk_kernel
+constexpr int kKeyBatch = 8;                   // keys per thread loaded together
+
+// The whole top-k of one (b, j) per workgroup.  One workgroup reads a head's
+// scores at about one CU's L2 rate, which costs less than a second launch and
+// the round trip of bitmap and candidates through memory (32k, 8
+// heads: classification 4.8 us, final 8.3 us and the gap between them before,
+// 12.4 us now; 1k, one head: 3.0 + 3.9 us, now 4.7 us).  Short
+// prefixes are bound by the chain of barriers, so the block scans use DPP
+// within the waves and one barrier each.
+__global__ void __launch_bounds__(kTopkThreads)
+topk_kernel(const float* __restrict__ S, const uint32_t* __restrict__ hist,
+            uint32_t* __restrict__ tws, int32_t* __restrict__ idx, int P, int k) {
+  __shared__ TopkShared sh;
+  __shared__ uint2 lcand[kTopkWaves * kLdsCap];
+  __shared__ __attribute__((aligned(8))) uint32_t xgt[kMapWords], xeq[kMapWords];
+  const int bj = blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const float* Sj = S + (size_t)bj * P;
+  float f[kKeyBatch];
+#pragma unroll
+  for (int i = 0; i < kKeyBatch; ++i)   // the first batch, in flight during the bin search
+    f[i] = Sj[min(i * kTopkThreads + (int)threadIdx.x, P - 1)];
+  const int W = (P + 31) / 32;
+  for (int x = threadIdx.x; x < W; x += kTopkThreads) xeq[x] = 0u;
+  hist_bin(hist, bj, k, sh);
+  const uint32_t bin = sh.sel_bin;
+  const int need = sh.sel_rem;
+  // the wave's list: at most one entry per key it classifies, so the waves'
+  // shares of the workspace (P entries in all) never meet
+  Cands cs;
+  cs.lds = lcand + w * kLdsCap;
+  cs.ws = topk_ws(tws, bj, P).cand + (size_t)(P / kTopkThreads) * 64 * w + min(64 * w, P % kTopkThreads);
+  cs.n = 0;
+  // order keys of the bin: [k_lo, k_hi)  (k_hi wraps to 0 for the last bin)
+  const uint32_t k_lo = bin << kHistShift, k_last = k_lo | ((1u << kHistShift) - 1u);
+  for (int p0 = 0; p0 < P; p0 += kKeyBatch * kTopkThreads) {
+    uint32_t u[kKeyBatch];
+#pragma unroll
+    for (int i = 0; i < kKeyBatch; ++i) u[i] = order_key(f[i]);
+    if (p0 + kKeyBatch * kTopkThreads < P) {
+#pragma unroll
+      for (int i = 0; i < kKeyBatch; ++i)
+        f[i] = Sj[min(p0 + (kKeyBatch + i) * kTopkThreads + (int)threadIdx.x, P - 1)];
+    }
+    uint32_t bits_lo = 0u, bits_hi = 0u;   // lane i: batch i's "in a higher bin" bits
+#pragma unroll
+    for (int i = 0; i < kKeyBatch; ++i) {
+      const int pw = p0 + i * kTopkThreads + w * 64;   // the wave's first position
+      if (pw >= P) break;
+      const uint64_t in = P - pw >= 64 ? ~0ull : (1ull << (P - pw)) - 1ull;
+      const uint64_t mg = __ballot(u[i] > k_last) & in;
+      const uint64_t mc = __ballot(u[i] >= k_lo && u[i] <= k_last) & in;
+      bits_lo = lane == i ? (uint32_t)mg : bits_lo;
+      bits_hi = lane == i ? (uint32_t)(mg >> 32) : bits_hi;
+      if (mc) {
+        if ((mc >> lane) & 1ull) {
+          const int r = cs.n + (int)__builtin_amdgcn_mbcnt_hi(
+                                   (uint32_t)(mc >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mc, 0u));
+          const uint2 e = make_uint2(u[i], (uint32_t)(pw + lane));
+          if (r < kLdsCap) cs.lds[r] = e;
+          else cs.ws[r] = e;
+        }
+        cs.n += (int)__popcll(mc);
+      }
+    }
+    const int pl = p0 + lane * kTopkThreads + w * 64;   // lane i writes batch i's two words
+    if (lane < kKeyBatch && pl < P)
+      *reinterpret_cast<uint2*>(&xgt[pl / 32]) = make_uint2(bits_lo, bits_hi);
+  }
+  __threadfence_block();   // list entries are read by other lanes of the wave
+  __syncthreads();
+  int need_eq;
+  const uint32_t T = cand_threshold(cs, bin, need, sh, need_eq);
+  for (int c = lane; c < cs.n; c += 64) {
+    const uint2 e = cand_at(cs, c);
+    const uint32_t bit = 1u << (e.y & 31);
+    if (e.x > T) atomicOr(&xgt[e.y >> 5], bit);
+    else if (e.x == T) atomicOr(&xeq[e.y >> 5], bit);
+  }
+  __syncthreads();
+  uint32_t o_base = 0, eq_base = 0;
+  for (int x0 = 0; x0 < W; x0 += kTopkThreads) {
+    const int x = x0 + (int)threadIdx.x;
+    const bool ok = x < W;
+    emit_words(ok ? xgt[x] : 0u, ok ? xeq[x] : 0u, x, need_eq, k, idx + (size_t)bj * k, o_base,
+               eq_base, sh);
+  }
+}
+
+// Final top-k of a prefix longer than kWholeKeys, one workgroup per (b, j):
 //  1. the bin of the k-th largest key (from the classification) and the
-//     candidates into LDS: the first kCandLds list entries are loaded
-//     together with the count (more candidates, in crowded or tied bins, are
-//     read from the workspace instead);
+//     candidates, of which each wave takes a contiguous share (its first
+//     kLdsCap into LDS);
 //  2. two digit passes over the candidates give T and how many keys equal
 //     to T to take;
 //  3. per window of kMapWords bitmap words: candidates above T and equal to
@@ -416,35 +525,27 @@ __device__ __forceinline__ void cand_digit_pass(const uint2* cand, int nc, uint3
 //     thread and round, the positions in higher bins plus the marked ones
 //     above T plus the lowest positions equal to T are written in ascending
 //     order.
-constexpr int kCandLds = 2048;
-constexpr int kMapWords = 4096;   // bitmap words per window (131072 positions)
 __global__ void __launch_bounds__(kTopkThreads)
 topk_final_kernel(uint32_t* __restrict__ tws, int32_t* __restrict__ idx, int P, int k) {
   __shared__ TopkShared sh;
-  __shared__ uint2 lcand[kCandLds];
+  __shared__ uint2 lcand[kTopkWaves * kLdsCap];
   __shared__ uint32_t xgt[kMapWords], xeq[kMapWords];
   const int bj = blockIdx.x;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const TopkWs f = topk_ws(tws, bj, P);
   const uint4 hdr = *reinterpret_cast<const uint4*>(f.ncand);
-  constexpr int kPre = kCandLds / kTopkThreads;
-  uint2 pre[kPre];   // list entries loaded before the count is known (in bounds: P entries)
-#pragma unroll
-  for (int i = 0; i < kPre; ++i) pre[i] = f.cand[min((int)threadIdx.x + i * kTopkThreads, P - 1)];
-  const int nc = (int)min(hdr.x, (uint32_t)P);
   const uint32_t bin = hdr.y;
   const int need = (int)hdr.z;
-  const uint2* cand = f.cand;
-  if (nc <= kCandLds) {
-#pragma unroll
-    for (int i = 0; i < kPre; ++i) lcand[threadIdx.x + i * kTopkThreads] = pre[i];
-    cand = lcand;
-    __syncthreads();
-  }
-  cand_digit_pass(cand, nc, bin, kDigitBits, need, sh);
-  const uint32_t d1 = sh.sel_bin;
-  cand_digit_pass(cand, nc, (bin << kDigitBits) | d1, 0, sh.sel_rem, sh);
-  const uint32_t T = (bin << (2 * kDigitBits)) | (d1 << kDigitBits) | sh.sel_bin;
-  const int need_eq = sh.sel_rem;   // keys equal to T to take, lowest positions first
+  Cands cs;
+  const int nc = (int)min(hdr.x, (uint32_t)P), share = (nc + kTopkWaves - 1) / kTopkWaves;
+  const int c0 = min(nc, w * share);
+  cs.lds = lcand + w * kLdsCap;
+  cs.ws = f.cand + c0;
+  cs.n = min(nc, c0 + share) - c0;
+  for (int c = lane; c < min(cs.n, kLdsCap); c += 64) cs.lds[c] = cs.ws[c];
+  __syncthreads();
+  int need_eq;
+  const uint32_t T = cand_threshold(cs, bin, need, sh, need_eq);
 
   int32_t* out = idx + (size_t)bj * k;
   uint32_t o_base = 0, eq_base = 0;
@@ -453,8 +554,8 @@ topk_final_kernel(uint32_t* __restrict__ tws, int32_t* __restrict__ idx, int P, 
     const int m1 = min(W, m0 + kMapWords);
     for (int x = threadIdx.x; x < kMapWords; x += kTopkThreads) xgt[x] = xeq[x] = 0u;
     __syncthreads();
-    for (int c = threadIdx.x; c < nc; c += kTopkThreads) {
-      const uint2 e = cand[c];
+    for (int c = lane; c < cs.n; c += 64) {
+      const uint2 e = cand_at(cs, c);
       const int x = (int)(e.y >> 5);
       if (x < m0 || x >= m1) continue;
       const uint32_t bit = 1u << (e.y & 31);
@@ -465,29 +566,8 @@ topk_final_kernel(uint32_t* __restrict__ tws, int32_t* __restrict__ idx, int P, 
     for (int x0 = m0; x0 < m1; x0 += kTopkThreads) {
       const int x = x0 + (int)threadIdx.x;
       const bool ok = x < m1;
-      uint32_t e = ok ? xeq[x - m0] : 0u;
-      const uint32_t g = ok ? f.gt[x] | xgt[x - m0] : 0u;
-      const int ne = __popc(e);
-      uint32_t eq_tot;
-      const int eq_before = (int)(eq_base + block_prefix_excl((uint32_t)ne, sh, eq_tot));
-      int keep = max(0, min(ne, need_eq - eq_before));
-      uint32_t kept = 0;
-      for (; keep > 0; --keep) {   // the lowest `keep` positions equal to T
-        const uint32_t low = e & (0u - e);
-        kept |= low;
-        e ^= low;
-      }
-      uint32_t sel = g | kept;
-      uint32_t sel_tot;
-      uint32_t o = o_base + block_prefix_excl((uint32_t)__popc(sel), sh, sel_tot);
-      while (sel) {
-        const int b = __builtin_ctz(sel);
-        if (o < (uint32_t)k) out[o] = x * 32 + b;   // never more than k
-        ++o;
-        sel &= sel - 1u;
-      }
-      o_base += sel_tot;
-      eq_base += eq_tot;
+      emit_words(ok ? f.gt[x] | xgt[x - m0] : 0u, ok ? xeq[x - m0] : 0u, x, need_eq, k, out, o_base,
+                 eq_base, sh);
     }
     __syncthreads();   // the window's bitmaps are read before the next window clears them
   }
@@ -497,33 +577,62 @@ topk_final_kernel(uint32_t* __restrict__ tws, int32_t* __restrict__ idx, int P, 
 
 size_t select_topk_ws_bytes(int BH, int P) { return (size_t)BH * topk_ws_words(P) * 4; }
 
-hipError_t launch_select(const hyq_shape& s, const hyq_sizes& z, const uint16_t* Q,
-                         const uint16_t* K, int32_t* idx, float* scores, float* qsum,
-                         uint32_t* hist, uint32_t* tws, float* cm_ws, hipStream_t st) {
-  if (z.k == 0) return hipSuccess;
+namespace {
+
+template <int QFMT>
+void launch_tail_proxy(const hyq_shape& s, const uint16_t* Q, float* qsum, uint32_t* hist,
+                       uint32_t* tws, int t, int P, const QuantQ& qq, hipStream_t st) {
+  const int BHq = s.B * s.Hq, n_tail = BHq * (kHeadDim / kTailCh);
+  static_assert(kTailThreads == kQuantThreads, "both kinds of workgroup share the launch");
+  tail_proxy_kernel<QFMT><<<n_tail + qq.count, kTailThreads, 0, st>>>(
+      Q, qsum, hist, tws, BHq, s.Hq / s.Hkv, s.L, t, P, n_tail, qq);
+}
+
+template <int QFMT>
+hipError_t launch_select_t(const hyq_shape& s, const hyq_sizes& z, const uint16_t* Q,
+                           const uint16_t* K, int32_t* idx, float* scores, float* qsum,
+                           uint32_t* hist, uint32_t* tws, float* cm_ws, const QuantQ& qq,
+                           hipStream_t st) {
   const int g = s.Hq / s.Hkv;
   const int t = s.window < s.L ? s.window : s.L;
   const int BH = s.B * s.Hkv;
   // (KV head, key chunk) with the head index fastest: workgroups are spread
   // over the XCDs round-robin, so with B*Hkv a multiple of 8 every chunk of a
-  // head (and its final top-k workgroup) runs on one XCD and shares that
-  // XCD's L2.
+  // head (and its top-k workgroup) runs on one XCD and shares that XCD's L2.
   if (s.selector == HYQ_SEL_COLMASS) {
-    hist_zero_kernel<<<BH, 256, 0, st>>>(hist, tws, z.P);
-    const hipError_t e = launch_colmass_scores(s, z, Q, K, scores, cm_ws, st);
+    const hipError_t e = launch_colmass_scores(s, z, Q, K, scores, hist, tws, topk_ws_words(z.P),
+                                               cm_ws, st);
     if (e != hipSuccess) return e;
-    hist_kernel<<<dim3(BH, (z.P + kHistThreads - 1) / kHistThreads), kHistThreads, 0, st>>>(
-        scores, hist, z.P);
+    launch_quant_q(qq, st);
   } else {
-    tail_proxy_kernel<<<dim3(s.B * s.Hq, kHeadDim / kTailCh), kTailThreads, 0, st>>>(
-        Q, qsum, hist, tws, s.Hq, s.Hkv, s.L, t, z.P);
+    launch_tail_proxy<QFMT>(s, Q, qsum, hist, tws, t, z.P, qq, st);
     score_kernel<<<dim3(BH, (z.P + kScoreRows - 1) / kScoreRows), kScoreThreads, 0, st>>>(
         K, qsum, scores, hist, g, s.L, z.P);
   }
-  const dim3 cg(BH, (z.P + kTopkThreads - 1) / kTopkThreads);
-  topk_classify_kernel<<<cg, kTopkThreads, 0, st>>>(scores, hist, tws, z.P, z.k);
-  topk_final_kernel<<<BH, kTopkThreads, 0, st>>>(tws, idx, z.P, z.k);
+  if (z.P <= kWholeKeys) {
+    topk_kernel<<<BH, kTopkThreads, 0, st>>>(scores, hist, tws, idx, z.P, z.k);
+  } else {
+    const dim3 cg(BH, (z.P + kTopkThreads - 1) / kTopkThreads);
+    topk_classify_kernel<<<cg, kTopkThreads, 0, st>>>(scores, hist, tws, z.P, z.k);
+    topk_final_kernel<<<BH, kTopkThreads, 0, st>>>(tws, idx, z.P, z.k);
+  }
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_select(const hyq_shape& s, const hyq_sizes& z, const uint16_t* Q,
+                         const uint16_t* K, int32_t* idx, float* scores, float* qsum,
+                         uint32_t* hist, uint32_t* tws, float* cm_ws, const QuantQ* qq,
+                         hipStream_t st) {
+  if (z.k == 0) return hipSuccess;
+  const QuantQ q = qq ? *qq : QuantQ{};   // none: no blocks
+#define HYQ_SELECT(F) \
+  launch_select_t<F>(s, z, Q, K, idx, scores, qsum, hist, tws, cm_ws, q, st)
+  return q.fmt == HYQ_FMT_FP4Q6 ? HYQ_SELECT(HYQ_FMT_FP4Q6)
+         : q.fmt == HYQ_FMT_INT ? HYQ_SELECT(HYQ_FMT_INT)
+                                : HYQ_SELECT(HYQ_FMT_FP8);
+#undef HYQ_SELECT
 }
 
 }  // namespace hyq
