@@ -25,6 +25,12 @@
 // compares positions with t - W, and the full-precision list also carries the
 // quantizable keys of the workgroup's band, each seen by W rows.
 //
+// Launches too small to fill the chip that way split the keys as well, or
+// take smaller workgroups (attn_shape.h): two groups of 4 waves per
+// workgroup, each with its own LDS rings and every other tile of the same 4
+// units, merged at the end; 4-wave workgroups, two per CU; or one unit per
+// workgroup with the keys split over its 8 waves (attn_prefill_split_kernel).
+//
 // Register layout (32x32 MFMA, wave64): lane l, accumulator register r holds
 // row (r/4)*8 + (l/32)*4 + r%4 and column l%32.  With keys as rows (S^T),
 // each lane owns one query (column) and 16 keys per 32-key half; those 16
@@ -49,6 +55,7 @@
 // The accumulator holds O * l / sVref; the row sum l adds P' / fm per tile
 // (from the same f16 values that enter the MFMA).  An all-zero V block
 // (sV = 0) folds nothing.
+#include "attn_shape.h"
 #include "codes_dev.h"
 #include "hyq_internal.h"
 
@@ -59,6 +66,7 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -67,16 +75,9 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 
 constexpr int kTile = 64;
-#ifndef HYQ_ATTN_WAVES
-#define HYQ_ATTN_WAVES 8
-#endif
-constexpr int kWaves = HYQ_ATTN_WAVES;    // waves per workgroup (kWaves / 4 per SIMD)
-constexpr int kThreads = kWaves * 64;
-constexpr int kWgPerCu = 8 / kWaves;      // workgroups per CU (two waves per SIMD)
 // 16-byte chunks of one staged tile: 8-bit K and V tiles are 512 chunks, 4-bit 256
 constexpr int kChunks8 = kTile * kHeadDim / 16;
 constexpr int kChunks4 = kChunks8 / 2;
-static_assert(kChunks8 % kThreads == 0, "8-bit tile chunks must split evenly");
 constexpr float kLazy = 8.0f;             // general path: rescale only when the max grows by > 2^8
 constexpr float kFastMax = 32768.0f;      // fast path: largest accepted weight sum of a lane
 constexpr float kLog2e = 1.4426950408889634f;
@@ -182,22 +183,24 @@ __device__ __forceinline__ int kswz4(int row, int chunk) {
 }
 
 // (native vectors: aggregate copies of HIP's uint4 would go through memory)
-// Chunks per thread: 8-bit tiles split evenly; a 4-bit tile has one chunk for
-// each of its first 256 threads, and the other threads (if any) repeat them
-// (same data to the same LDS bytes), which keeps staging branch-free.
-template <int BITS>
+// Chunks per thread of an NT-thread workgroup: 8-bit tiles split evenly; a
+// 4-bit tile has one chunk for each of its first 256 threads, and the other
+// threads (if any) repeat them (same data to the same LDS bytes), which keeps
+// staging branch-free.
+template <int BITS, int NT>
 constexpr int chunks_per_thread() {
-  return BITS == 8 ? kChunks8 / kThreads : (kChunks4 >= kThreads ? kChunks4 / kThreads : 1);
+  static_assert(kChunks8 % NT == 0 && NT >= kChunks4, "tile chunks must split evenly");
+  return BITS == 8 ? kChunks8 / NT : 1;
 }
-template <int BITS>
+template <int BITS, int NT>
 __device__ __forceinline__ int chunk_id(int tid, int i) {
-  return BITS == 8 ? tid + i * kThreads : ((tid + i * kThreads) & (kChunks4 - 1));
+  return BITS == 8 ? tid + i * NT : (tid & (kChunks4 - 1));
 }
 
-template <int BITS>
+template <int BITS, int NT>
 struct StageRegs {
-  v4u k[chunks_per_thread<BITS>()];   // 16-byte chunks chunk_id(tid, i) of a K tile
-  v4u v[chunks_per_thread<BITS>()];   // same for a V tile
+  v4u k[chunks_per_thread<BITS, NT>()];   // 16-byte chunks chunk_id(tid, i) of a K tile
+  v4u v[chunks_per_thread<BITS, NT>()];   // same for a V tile
   int32_t meta;                 // threads 0..63: kq_pos; 64, 65: sK, sV bits (K's tile)
 };
 
@@ -356,7 +359,8 @@ struct SegA {
   const int32_t* kq0;
   const float* ks0;
   const float* vs0;
-  int n;              // quantized tiles to scan
+  int n;              // quantized tiles to scan, of which this group takes
+  int grp;            // grp, grp + S, ...
   int t0;             // first query row of the wave
   float cq;           // alpha * log2(e) * s_Q
   float inv_vref;
@@ -364,19 +368,19 @@ struct SegA {
 };
 
 // K codes and metadata of tile tk, V codes of tile tv.
-template <int BITS>
-__device__ __forceinline__ void stage_load(StageRegs<BITS>& r, const SegA& a, int tk, int tv,
+template <int BITS, int NT>
+__device__ __forceinline__ void stage_load(StageRegs<BITS, NT>& r, const SegA& a, int tk, int tv,
                                            int tid) {
   constexpr int kRow = BITS == 8 ? kHeadDim : kHeadDim / 2;
   constexpr int vRow = BITS == 8 ? kTile : kTile / 2;
-  constexpr int n = chunks_per_thread<BITS>();
+  constexpr int n = chunks_per_thread<BITS, NT>();
   const int t = tk;
   const v4u* kc = reinterpret_cast<const v4u*>(a.kc0 + (size_t)tk * kTile * kRow);
   const v4u* vc = reinterpret_cast<const v4u*>(a.vc0 + (size_t)tv * kHeadDim * vRow);
 #pragma unroll
-  for (int i = 0; i < n; ++i) r.k[i] = kc[chunk_id<BITS>(tid, i)];
+  for (int i = 0; i < n; ++i) r.k[i] = kc[chunk_id<BITS, NT>(tid, i)];
 #pragma unroll
-  for (int i = 0; i < n; ++i) r.v[i] = vc[chunk_id<BITS>(tid, i)];
+  for (int i = 0; i < n; ++i) r.v[i] = vc[chunk_id<BITS, NT>(tid, i)];
   // wave 0: kq_pos; wave 1: lane 0 sK, lane 1 sV; the rest reload sV
   // (choices uniform per wave or between two uniform addresses: no branch)
   const int w = tid >> 6, lane = tid & 63;
@@ -390,18 +394,18 @@ __device__ __forceinline__ void stage_load(StageRegs<BITS>& r, const SegA& a, in
 // int8 K: chunk q = row*8 + j goes to the swizzled slot of (row, j).  4-bit
 // K: chunk tid holds 32 channels of row tid/4, expanded to int8 (16*code)
 // and stored as two chunks.  V: f16 [128][kVPitch] in the permuted key order.
-template <int BITS, int FMT>
-__device__ __forceinline__ void stage_store(KBuf& kb, VBuf& vb, const StageRegs<BITS>& r, int tid,
+template <int BITS, int FMT, int NT>
+__device__ __forceinline__ void stage_store(KBuf& kb, VBuf& vb, const StageRegs<BITS, NT>& r, int tid,
                                             const VScale& vs) {
   if (BITS == 8) {
 #pragma unroll
-    for (int i = 0; i < chunks_per_thread<BITS>(); ++i) {
-      const int q = chunk_id<BITS>(tid, i);
+    for (int i = 0; i < chunks_per_thread<BITS, NT>(); ++i) {
+      const int q = chunk_id<BITS, NT>(tid, i);
       *reinterpret_cast<v4u*>(kb.k + kswz(q >> 3, q & 7)) = r.k[i];
     }
 #pragma unroll
-    for (int i = 0; i < chunks_per_thread<BITS>(); ++i) {
-      const int q = chunk_id<BITS>(tid, i);
+    for (int i = 0; i < chunks_per_thread<BITS, NT>(); ++i) {
+      const int q = chunk_id<BITS, NT>(tid, i);
       const int d = q >> 2, kg = q & 3;   // channel d, keys kg*16 .. +16
       const v4u w = r.v[i];
       uint32_t h[8];
@@ -416,7 +420,7 @@ __device__ __forceinline__ void stage_store(KBuf& kb, VBuf& vb, const StageRegs<
   } else if constexpr (kv_fp4(FMT)) {
     // E2M1 K: the 16-byte chunk as it is (the MFMA reads 4-bit operands);
     // V: E2M1 -> f16 times 2^e, two codes per conversion, exact
-    const int q4 = chunk_id<BITS>(tid, 0);
+    const int q4 = chunk_id<BITS, NT>(tid, 0);
     *reinterpret_cast<v4u*>(kb.k + kswz4(q4 >> 2, q4 & 3)) = r.k[0];
     const int d = q4 >> 1, kh = q4 & 1;   // channel d, keys kh*32 .. +32 (16 B packed)
     const v4u w = r.v[0];
@@ -431,7 +435,7 @@ __device__ __forceinline__ void stage_store(KBuf& kb, VBuf& vb, const StageRegs<
       *reinterpret_cast<v4u*>(dst + 16) = v4u{h[2], h[3], h[6], h[7]};
     }
   } else {
-    const int q4 = chunk_id<BITS>(tid, 0);
+    const int q4 = chunk_id<BITS, NT>(tid, 0);
     {
       const int row = q4 >> 2, j4 = q4 & 3;
       const v4u w = r.k[0];
@@ -500,71 +504,79 @@ __device__ __forceinline__ void fp_resolve(const FpList& f, int e, int32_t w, in
 }
 
 // A full-precision tile in registers.  K: thread tid holds the 16-byte
-// chunks q = tid + i * kThreads (key q / 16, channels 8 * (q % 16) ..), with
-// the key's position and last row.  V: item q = tid + i * kThreads is the
+// chunks q = tid + i * NT (key q / 16, channels 8 * (q % 16) ..), with
+// the key's position and last row.  V: item q = tid + i * NT is the
 // chunk q / 32 of the key pair (2 * (q % 32), +1), so that one LDS store
 // writes both keys of a channel (adjacent V^T slots) and the 64 lanes of a
 // wave (32 pairs, two chunks) hit distinct banks.  Also the position words of
 // the same keys of the following tile.
-constexpr int kFpPairs = kTile * 16 / kThreads;
-constexpr int kFpVItems = (kTile / 2) * 16 / kThreads;
-static_assert((kTile * 16) % kThreads == 0 && ((kTile / 2) * 16) % kThreads == 0,
-              "full-precision chunks must split evenly");
+// Thread index within its group of NT threads (a workgroup is one or two groups).
+template <int NT>
+__device__ __forceinline__ int group_tid() { return (int)threadIdx.x & (NT - 1); }
+template <int NT>
 struct FpRegs {
-  v4u k[kFpPairs], v[2 * kFpVItems];
-  int32_t pos[kFpPairs], hi[kFpPairs], vpos[2 * kFpVItems];
-  int32_t wnext[kFpPairs], vwnext[2 * kFpVItems];
+  static constexpr int kPairs = kTile * 16 / NT, kVItems = (kTile / 2) * 16 / NT;
+  static_assert((kTile * 16) % NT == 0 && ((kTile / 2) * 16) % NT == 0,
+                "full-precision chunks must split evenly");
+  v4u k[kPairs], v[2 * kVItems];
+  int32_t pos[kPairs], hi[kPairs], vpos[2 * kVItems];
+  int32_t wnext[kPairs], vwnext[2 * kVItems];
 };
-__device__ __forceinline__ int fp_kkey(int i) { return ((int)threadIdx.x + i * kThreads) >> 4; }
+template <int NT>
+__device__ __forceinline__ int fp_kkey(int i) { return (group_tid<NT>() + i * NT) >> 4; }
+template <int NT>
 __device__ __forceinline__ int fp_vkey(int i, int s) {
-  return 2 * (((int)threadIdx.x + i * kThreads) & 31) + s;
+  return 2 * ((group_tid<NT>() + i * NT) & 31) + s;
 }
-__device__ __forceinline__ int fp_vchunk(int i) { return ((int)threadIdx.x + i * kThreads) >> 5; }
+template <int NT>
+__device__ __forceinline__ int fp_vchunk(int i) { return (group_tid<NT>() + i * NT) >> 5; }
 
 // Position words of tile ft (before its first fp_load).
-__device__ __forceinline__ void fp_load_words(FpRegs& r, const FpList& f, int ft) {
+template <int NT>
+__device__ __forceinline__ void fp_load_words(FpRegs<NT>& r, const FpList& f, int ft) {
 #pragma unroll
-  for (int i = 0; i < kFpPairs; ++i) r.wnext[i] = *fp_src(f, ft * kTile + fp_kkey(i));
+  for (int i = 0; i < FpRegs<NT>::kPairs; ++i) r.wnext[i] = *fp_src(f, ft * kTile + fp_kkey<NT>(i));
 #pragma unroll
-  for (int i = 0; i < kFpVItems; ++i)
+  for (int i = 0; i < FpRegs<NT>::kVItems; ++i)
 #pragma unroll
-    for (int s = 0; s < 2; ++s) r.vwnext[2 * i + s] = *fp_src(f, ft * kTile + fp_vkey(i, s));
+    for (int s = 0; s < 2; ++s) r.vwnext[2 * i + s] = *fp_src(f, ft * kTile + fp_vkey<NT>(i, s));
 }
 
 // Load the rows of tile ft (padding rows read row 0, zeroed at the store)
-// from the position words loaded earlier, then the words of tile ft+1.
+// from the position words loaded earlier, then the words of the group's next
+// tile ft + S.
 // Tiles past the end are all padding.
-__device__ __forceinline__ void fp_load(FpRegs& r, const FpList& f, const uint16_t* __restrict__ Kh,
+template <int NT, int S>
+__device__ __forceinline__ void fp_load(FpRegs<NT>& r, const FpList& f, const uint16_t* __restrict__ Kh,
                                         const uint16_t* __restrict__ Vh, int ft, int L) {
 #pragma unroll
-  for (int i = 0; i < kFpPairs; ++i) {
+  for (int i = 0; i < FpRegs<NT>::kPairs; ++i) {
     int p, hi;
-    fp_resolve(f, ft * kTile + fp_kkey(i), r.wnext[i], p, hi);
+    fp_resolve(f, ft * kTile + fp_kkey<NT>(i), r.wnext[i], p, hi);
     r.pos[i] = p;
     r.hi[i] = hi;
     const size_t row = (unsigned)p < (unsigned)L ? (size_t)p : 0;
-    r.k[i] = reinterpret_cast<const v4u*>(Kh + row * kHeadDim)[((int)threadIdx.x + i * kThreads) & 15];
+    r.k[i] = reinterpret_cast<const v4u*>(Kh + row * kHeadDim)[(group_tid<NT>() + i * NT) & 15];
   }
 #pragma unroll
-  for (int i = 0; i < kFpVItems; ++i)
+  for (int i = 0; i < FpRegs<NT>::kVItems; ++i)
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       int p, hi;
-      fp_resolve(f, ft * kTile + fp_vkey(i, s), r.vwnext[2 * i + s], p, hi);
+      fp_resolve(f, ft * kTile + fp_vkey<NT>(i, s), r.vwnext[2 * i + s], p, hi);
       r.vpos[2 * i + s] = p;
       const size_t row = (unsigned)p < (unsigned)L ? (size_t)p : 0;
-      r.v[2 * i + s] = reinterpret_cast<const v4u*>(Vh + row * kHeadDim)[fp_vchunk(i)];
+      r.v[2 * i + s] = reinterpret_cast<const v4u*>(Vh + row * kHeadDim)[fp_vchunk<NT>(i)];
     }
-  fp_load_words(r, f, ft + 1);
+  fp_load_words<NT>(r, f, ft + S);
 }
 
-// V^T stores of one key pair (adjacent slots from the even key's) and one
+// V^T stores of one key pair (adjacent slots from `slot` on) and one
 // 16-byte chunk: channel d gets the 32-bit word (f16 of key 2m, of key 2m+1)
 // of V / sVref (sVref a power of two: exact for bf16 values of that range,
 // down to the f16 subnormals).  Returns the largest |V| of the pair's chunk.
-__device__ __forceinline__ float fp_store_vpair(FBuf& b, v4u v0, v4u v1, int key0, int chunk,
+__device__ __forceinline__ float fp_store_vpair(uint8_t* vt, v4u v0, v4u v1, int slot, int chunk,
                                                 float inv_vref) {
-  const int slot = vslot(key0);
   float mx = 0.0f;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -574,8 +586,8 @@ __device__ __forceinline__ float fp_store_vpair(FBuf& b, v4u v0, v4u v1, int key
     mx = fmaxf(mx, fmaxf(fabsf(a0), fabsf(a1)));
     mx = fmaxf(mx, fmaxf(fabsf(b0), fabsf(b1)));
     const v2f lo = {a0 * inv_vref, a1 * inv_vref}, hi = {b0 * inv_vref, b1 * inv_vref};
-    *reinterpret_cast<v2h*>(b.v + d * kVPitch + slot * 2) = __builtin_convertvector(lo, v2h);
-    *reinterpret_cast<v2h*>(b.v + (d + 1) * kVPitch + slot * 2) = __builtin_convertvector(hi, v2h);
+    *reinterpret_cast<v2h*>(vt + d * kVPitch + slot * 2) = __builtin_convertvector(lo, v2h);
+    *reinterpret_cast<v2h*>(vt + (d + 1) * kVPitch + slot * 2) = __builtin_convertvector(hi, v2h);
   }
   return mx;
 }
@@ -584,10 +596,11 @@ __device__ __forceinline__ float fp_store_vpair(FBuf& b, v4u v0, v4u v1, int key
 // positions and last rows.  A V ratio outside the f16 range records
 // (tile << 8) | (largest biased exponent of |V|) in ovf (a NaN is not
 // recorded: it stays a NaN in f16).
-__device__ __forceinline__ void fp_store(FBuf& b, const FpRegs& r, float inv_vref, int tag, int L) {
+template <int NT>
+__device__ __forceinline__ void fp_store(FBuf& b, const FpRegs<NT>& r, float inv_vref, int tag, int L) {
 #pragma unroll
-  for (int i = 0; i < kFpPairs; ++i) {
-    const int e = fp_kkey(i), col = ((int)threadIdx.x + i * kThreads) & 15;
+  for (int i = 0; i < FpRegs<NT>::kPairs; ++i) {
+    const int e = fp_kkey<NT>(i), col = (group_tid<NT>() + i * NT) & 15;
     const unsigned keep = (unsigned)r.pos[i] < (unsigned)L ? 0xffffffffu : 0u;
     *reinterpret_cast<v4u*>(b.k + e * kKPitchBf + col * 16) = r.k[i] & keep;
     if (col == 0) {
@@ -597,29 +610,30 @@ __device__ __forceinline__ void fp_store(FBuf& b, const FpRegs& r, float inv_vre
   }
   float mx = 0.0f;
 #pragma unroll
-  for (int i = 0; i < kFpVItems; ++i) {
+  for (int i = 0; i < FpRegs<NT>::kVItems; ++i) {
     const unsigned k0 = (unsigned)r.vpos[2 * i] < (unsigned)L ? 0xffffffffu : 0u;
     const unsigned k1 = (unsigned)r.vpos[2 * i + 1] < (unsigned)L ? 0xffffffffu : 0u;
-    mx = fmaxf(mx, fp_store_vpair(b, r.v[2 * i] & k0, r.v[2 * i + 1] & k1, fp_vkey(i, 0),
-                                  fp_vchunk(i), inv_vref));
+    mx = fmaxf(mx, fp_store_vpair(b.v, r.v[2 * i] & k0, r.v[2 * i + 1] & k1,
+                                  vslot(fp_vkey<NT>(i, 0)), fp_vchunk<NT>(i), inv_vref));
   }
   if (!(mx * inv_vref <= 65504.0f)) atomicMax(&b.ovf, (tag << 8) | (int)(__float_as_uint(mx) >> 23));
 }
 
 // Rewrite the V^T of a published tile with a new sVref (positions from LDS).
+template <int NT>
 __device__ __forceinline__ void fp_restage_v(FBuf& b, const uint16_t* __restrict__ Vh, int L,
                                              float inv_vref) {
 #pragma unroll
-  for (int i = 0; i < kFpVItems; ++i) {
+  for (int i = 0; i < FpRegs<NT>::kVItems; ++i) {
     v4u vw[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const int p = b.pos[fp_vkey(i, s)];
+      const int p = b.pos[fp_vkey<NT>(i, s)];
       vw[s] = v4u{0u, 0u, 0u, 0u};
       if ((unsigned)p < (unsigned)L)
-        vw[s] = reinterpret_cast<const v4u*>(Vh + (size_t)p * kHeadDim)[fp_vchunk(i)];
+        vw[s] = reinterpret_cast<const v4u*>(Vh + (size_t)p * kHeadDim)[fp_vchunk<NT>(i)];
     }
-    fp_store_vpair(b, vw[0], vw[1], fp_vkey(i, 0), fp_vchunk(i), inv_vref);
+    fp_store_vpair(b.v, vw[0], vw[1], vslot(fp_vkey<NT>(i, 0)), fp_vchunk<NT>(i), inv_vref);
   }
 }
 
@@ -662,6 +676,16 @@ struct NState {
   float corr;     // rescale of acc still to apply: 2^(m_before - m)
   v16f acc[4];    // O^T accumulator, 4 groups of 32 channels
 };
+
+__device__ __forceinline__ void init_state(NState& st) {
+  st.m = kMinusBig;
+  st.l = 0.0f;
+  st.corr = 1.0f;
+#pragma unroll
+  for (int dg = 0; dg < 4; ++dg)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st.acc[dg][r] = 0.0f;
+}
 
 // Key index (0..63) of accumulator register r of half-tile kh for this lane.
 __device__ __forceinline__ int key_of(int kh, int r, int half) {
@@ -768,13 +792,17 @@ __device__ __forceinline__ void fp_softmax(NState& st, const v16f (&sf)[2], floa
 // general path moves the reference max, and it rescales on the spot.
 // PH = c % 4 is a template argument so that every LDS address is a per-lane
 // constant plus an immediate offset.
-template <int BITS, int FMT, int PH>
+template <int BITS, int FMT, int NT, int S, int PH>
 __device__ __forceinline__ void segA_tile(Smem& sm, const SegA& a, int c, const QFrag<FMT>& qf,
                                           NState& st, const v8h (&pprev)[4], v8h (&pcur)[4],
-                                          StageRegs<BITS>& sr, KFrag<FMT>& kf) {
+                                          StageRegs<BITS, NT>& sr, KFrag<FMT>& kf) {
   // 4-bit integer codes are staged as 16*code
   constexpr float kSub = (BITS == 8 || kv_fp4(FMT)) ? 1.0f : 0.0625f;
-  const int tid = threadIdx.x;
+  const int tid = group_tid<NT>();
+  // the group's c-th tile; past the end (loads, and with S = 2 the whole last
+  // step of the second group) the last tile again, in that step all hidden
+  auto tile = [&](int i) { return min(i * S + a.grp, a.n - 1); };
+  const bool dead = S > 1 && c * S + a.grp >= a.n;
   const KBuf& cur = sm.q.kb[PH];
   const VBuf& prv = sm.q.vb[(PH + 1) & 1];
   const float sk = __int_as_float(cur.pos[kMetaSK]) * kSub;
@@ -795,8 +823,8 @@ __device__ __forceinline__ void segA_tile(Smem& sm, const SegA& a, int c, const 
   // publish K(c+2) and V(c) (registers loaded during tile c-1) and load K(c+3)
   // and V(c+1); the conversion runs in the shadow of the MFMAs above.  Past
   // the end the last tile is staged again into the free buffers (no branch).
-  stage_store<BITS, FMT>(sm.q.kb[(PH + 2) % kKRing], sm.q.vb[PH & 1], sr, tid, vs);
-  stage_load<BITS>(sr, a, min(c + 3, a.n - 1), min(c + 1, a.n - 1), tid);
+  stage_store<BITS, FMT, NT>(sm.q.kb[(PH + 2) % kKRing], sm.q.vb[PH & 1], sr, tid, vs);
+  stage_load<BITS, NT>(sr, a, tile(c + 3), tile(c + 1), tid);
 
   // Fast path: weights against the current reference max, without the tile
   // max; accepted unless some lane's weights sum above kFastMax (then some
@@ -830,10 +858,10 @@ __device__ __forceinline__ void segA_tile(Smem& sm, const SegA& a, int c, const 
   // than sunk into the branch below that consumes them
   asm volatile("" : "+v"(pcur[0]), "+v"(pcur[1]), "+v"(pcur[2]), "+v"(pcur[3]), "+v"(ps));
   __builtin_amdgcn_s_setprio(0);
-  const bool diag = last > a.t0;
+  const bool diag = dead || last > a.t0;
   const bool redo = diag || __ballot(!(ps <= kFastMax)) != 0;
   if (redo) {
-    softmax_general(st, s, pcur, cqk, fm, diag, cur.pos, a.t0 + a.col, a.half);
+    softmax_general(st, s, pcur, cqk, fm, diag, cur.pos, dead ? -1 : a.t0 + a.col, a.half);
   } else {
     st.l = __builtin_fmaf(ps, __builtin_amdgcn_rcpf(fm), st.l);   // 1-ulp reciprocal
   }
@@ -843,8 +871,98 @@ __device__ __forceinline__ void segA_tile(Smem& sm, const SegA& a, int c, const 
   __syncthreads();
 }
 
-template <int BITS, int OUT_BF16, int FMT>
-__global__ void __launch_bounds__(kThreads, kWgPerCu)
+// Which keys the rows [t_first, t_last] of a workgroup see, and the reference
+// sVref of their head's V scales.  A quantized key at position p is seen by
+// rows t >= p + shift: shift = 0 for the fixed window, W for the per-query
+// band (whose rows see p in full precision instead).
+struct KeyPlan {
+  int shift, nvl, nq_tiles, fp_count, fp_base, nq0, nqb;
+  float vref;
+};
+template <int BITS, int FMT>
+__device__ __forceinline__ KeyPlan key_plan(const int32_t* __restrict__ vl,
+                                            const float* __restrict__ v_scale, int k, int P, int nQ,
+                                            int n_kvblk, int t_first, int t_last, int band_w) {
+  KeyPlan pl;
+  pl.shift = BITS == 16 ? 0 : band_w;
+  pl.nq0 = pl.nqb = 0;
+  pl.vref = 1.0f;
+  if (BITS == 16) {
+    pl.nvl = 0;
+    pl.nq_tiles = 0;
+    pl.fp_base = 0;
+    pl.fp_count = t_last + 1;
+    return pl;
+  }
+  const int lane = threadIdx.x & 63;
+  pl.nvl = count_le(vl, k, t_last);
+  const int tq_last = t_last - pl.shift;        // last quantized position any row sees
+  // (for the fixed window tq_last = t_last: the count is nvl, no second search)
+  const int nq_vis = tq_last < 0 ? 0 : (tq_last < P ? (tq_last + 1) -
+                                        (pl.shift == 0 ? pl.nvl : count_le(vl, k, tq_last)) : nQ);
+  pl.nq_tiles = min((nq_vis + kTile - 1) / kTile, n_kvblk);
+  pl.fp_base = P;
+  if (band_w > 0) {
+    // band keys of the workgroup's rows: positions [lo, t_last], lo from its first row
+    const int lo = max(0, t_first + 1 - band_w);
+    const int hi_q = min(t_last, P - 1);    // quantizable band keys: non-vertical in [lo, hi_q]
+    if (lo <= hi_q) {
+      pl.nq0 = lo - count_le(vl, k, lo - 1);    // non-vertical positions below lo
+      pl.nqb = (hi_q + 1) - count_le(vl, k, hi_q) - pl.nq0;
+    }
+    pl.fp_base = max(P, lo);
+  }
+  pl.fp_count = pl.nvl + pl.nqb + max(0, t_last + 1 - pl.fp_base);
+  // sVref: smallest power of two >= every V scale of this head
+  float mx = 0.0f;
+  for (int i = lane; i < n_kvblk; i += 64) mx = fmaxf(mx, v_scale[i]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  if (BITS == 4 && FMT == HYQ_FMT_INT) mx *= 0.0625f;
+  if (mx > 0.0f) {
+    int e;
+    frexpf(mx, &e);
+    e = max(-100, min(100, e));
+    pl.vref = ldexpf(1.0f, e);
+  }
+  return pl;
+}
+
+// The full-precision key list of a plan.
+__device__ __forceinline__ FpList fp_list(const KeyPlan& pl, const int32_t* vl, const int32_t* kq,
+                                          const uint16_t* Kh) {
+  FpList fl;
+  fl.vl = vl;
+  fl.kq = kq;
+  fl.dummy = reinterpret_cast<const int32_t*>(Kh);
+  fl.nvl = pl.nvl;
+  fl.nq0 = pl.nq0;
+  fl.nqb = pl.nqb;
+  fl.base = pl.fp_base;
+  fl.count = pl.fp_count;
+  fl.band_w = pl.shift;
+  return fl;
+}
+
+// Four consecutive output channels (values * sc) at element offset `at`.
+template <int OUT_BF16>
+__device__ __forceinline__ void store_out4(void* out, size_t at, float o0, float o1, float o2,
+                                           float o3) {
+  if (OUT_BF16) {
+    uint16_t* o = reinterpret_cast<uint16_t*>(out) + at;
+    const __bf16 b0 = (__bf16)o0, b1 = (__bf16)o1, b2 = (__bf16)o2, b3 = (__bf16)o3;
+    const uint32_t w0 = (uint32_t)__builtin_bit_cast(uint16_t, b0) |
+                        ((uint32_t)__builtin_bit_cast(uint16_t, b1) << 16);
+    const uint32_t w1 = (uint32_t)__builtin_bit_cast(uint16_t, b2) |
+                        ((uint32_t)__builtin_bit_cast(uint16_t, b3) << 16);
+    *reinterpret_cast<uint2*>(o) = make_uint2(w0, w1);
+  } else {
+    *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + at) = make_float4(o0, o1, o2, o3);
+  }
+}
+
+template <int BITS, int OUT_BF16, int FMT, int NW, int S>
+__global__ void __launch_bounds__(NW * S * 64, 8 / (NW * S))
 attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                     const uint16_t* __restrict__ V, const int32_t* __restrict__ idx,
                     const int8_t* __restrict__ q_codes, const float* __restrict__ q_scale,
@@ -852,26 +970,32 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
                     const uint8_t* __restrict__ v_codes, const float* __restrict__ v_scale,
                     const int32_t* __restrict__ kq_pos, void* __restrict__ out, int Hq, int Hkv,
                     int nbj, int L, int P, int k, int nQ, int n_qblk, int n_kvblk,
-                    float alpha_log2e, int band_w) {
-  __shared__ Smem sm;
+                    float alpha_log2e, int band_w, int fold) {
+  constexpr int NT = NW * 64;   // threads of a group
+  __shared__ Smem sms[S];
   const int g = Hq / Hkv;
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int grp = wv / NW, w = wv % NW;
+  Smem& sm = sms[grp];
   const int half = lane >> 5, col = lane & 31;
 
   // Work units of one KV head: (block rb of 32 rows, query head hh of the
-  // group), ordered by rb; a workgroup takes kWaves consecutive units, longest first.
+  // group), ordered by rb; a workgroup takes NW consecutive units (with S = 2
+  // both its groups take the same ones).  The first `fold` workgroups of a
+  // head come longest first, the rest shortest first.
   constexpr int kRows = 32;
   const int nrb = (L + kRows - 1) / kRows;
   const int units = g * nrb;
-  const int wg_per_bj = (units + kWaves - 1) / kWaves;
-  const int wgi = wg_per_bj - 1 - (int)blockIdx.x / nbj;
+  const int wg_per_bj = (units + NW - 1) / NW;
+  const int slot = (int)blockIdx.x / nbj;
+  const int wgi = slot < fold ? wg_per_bj - 1 - slot : slot - fold;
   const int bj = (int)blockIdx.x % nbj;
-  const int u = wgi * kWaves + w;
+  const int u = wgi * NW + w;
   const bool active = u < units;
   const int uu = active ? u : units - 1;   // an idle wave mirrors the last unit, stores nothing
   const int rb = uu / g, hh = uu % g;
-  const int u_last = min(wgi * kWaves + kWaves - 1, units - 1);
+  const int u_last = min(wgi * NW + NW - 1, units - 1);
   const int t_last = min(L - 1, (u_last / g) * kRows + kRows - 1);   // workgroup
   const int b = bj / Hkv, j = bj % Hkv, h = j * g + hh;
   const size_t bh = (size_t)b * Hq + h;
@@ -884,58 +1008,12 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
   const int32_t* vl = idx + (size_t)bj * k;
 
   NState st;
-  st.m = kMinusBig;
-  st.l = 0.0f;
-  st.corr = 1.0f;
-#pragma unroll
-  for (int dg = 0; dg < 4; ++dg)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) st.acc[dg][r] = 0.0f;
+  init_state(st);
 
-  // Which keys are visible to rows up to t_last.  A quantized key at
-  // position p is seen by rows t >= p + shift: shift = 0 for the fixed window,
-  // W for the per-query band (whose rows see p in full precision instead).
-  const int shift = BITS == 16 ? 0 : band_w;
-  int nvl, nq_tiles, fp_count, fp_base, nq0 = 0, nqb = 0;
-  float vref = 1.0f;
-  if (BITS == 16) {
-    nvl = 0;
-    nq_tiles = 0;
-    fp_base = 0;
-    fp_count = t_last + 1;
-  } else {
-    nvl = count_le(vl, k, t_last);
-    const int tq_last = t_last - shift;        // last quantized position any row sees
-    // (for the fixed window tq_last = t_last: the count is nvl, no second search)
-    const int nq_vis = tq_last < 0 ? 0 : (tq_last < P ? (tq_last + 1) -
-                                          (shift == 0 ? nvl : count_le(vl, k, tq_last)) : nQ);
-    nq_tiles = min((nq_vis + kTile - 1) / kTile, n_kvblk);
-    fp_base = P;
-    if (band_w > 0) {
-      // band keys of the workgroup's rows: positions [lo, t_last], lo from its first row
-      const int t0_wg = ((wgi * kWaves) / g) * kRows;
-      const int lo = max(0, t0_wg + 1 - band_w);
-      const int hi_q = min(t_last, P - 1);    // quantizable band keys: non-vertical in [lo, hi_q]
-      if (lo <= hi_q) {
-        nq0 = lo - count_le(vl, k, lo - 1);    // non-vertical positions below lo
-        nqb = (hi_q + 1) - count_le(vl, k, hi_q) - nq0;
-      }
-      fp_base = max(P, lo);
-    }
-    fp_count = nvl + nqb + max(0, t_last + 1 - fp_base);
-    // sVref: smallest power of two >= every V scale of this head
-    float mx = 0.0f;
-    for (int i = lane; i < n_kvblk; i += 64) mx = fmaxf(mx, v_scale[(size_t)bj * n_kvblk + i]);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    if (BITS == 4 && FMT == HYQ_FMT_INT) mx *= 0.0625f;
-    if (mx > 0.0f) {
-      int e;
-      frexpf(mx, &e);
-      e = max(-100, min(100, e));
-      vref = ldexpf(1.0f, e);
-    }
-  }
+  const KeyPlan pl = key_plan<BITS, FMT>(vl, v_scale + (size_t)bj * n_kvblk, k, P, nQ, n_kvblk,
+                                         ((wgi * NW) / g) * kRows, t_last, band_w);
+  const int shift = pl.shift, nq_tiles = pl.nq_tiles, fp_count = pl.fp_count;
+  float vref = pl.vref;
   float inv_vref = 1.0f / vref;
 
   // ---------------- segment A: quantized keys ----------------
@@ -950,6 +1028,7 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
     a.ks0 = k_scale + (size_t)bj * n_kvblk;
     a.vs0 = v_scale + (size_t)bj * n_kvblk;
     a.n = nq_tiles;
+    a.grp = grp;
     a.t0 = t0 - shift;   // rows t see quantized positions <= t - shift
     a.cq = alpha_log2e * q_scale[bh * n_qblk + t0 / kBlock];
     a.inv_vref = inv_vref;
@@ -963,15 +1042,17 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
     // prologue: K(0), K(1) into LDS, K(2) and V(0) into registers, the
     // fragments of K(0) read; the V buffer that tile 0 multiplies by zero
     // weights is cleared (no stale NaNs)
-    StageRegs<BITS> sr;
-    stage_load<BITS>(sr, a, 0, 0, threadIdx.x);
+    const int tid = group_tid<NT>(), steps = (nq_tiles + S - 1) / S;
+    auto tile = [&](int i) { return min(i * S + grp, nq_tiles - 1); };
+    StageRegs<BITS, NT> sr;
+    stage_load<BITS, NT>(sr, a, tile(0), 0, tid);
     const VScale unit = make_vscale(1.0f);   // the V written here is cleared below
-    stage_store<BITS, FMT>(sm.q.kb[0], sm.q.vb[1], sr, threadIdx.x, unit);
-    stage_load<BITS>(sr, a, min(1, nq_tiles - 1), 0, threadIdx.x);
-    stage_store<BITS, FMT>(sm.q.kb[1], sm.q.vb[1], sr, threadIdx.x, unit);
-    stage_load<BITS>(sr, a, min(2, nq_tiles - 1), 0, threadIdx.x);
+    stage_store<BITS, FMT, NT>(sm.q.kb[0], sm.q.vb[1], sr, tid, unit);
+    stage_load<BITS, NT>(sr, a, tile(1), 0, tid);
+    stage_store<BITS, FMT, NT>(sm.q.kb[1], sm.q.vb[1], sr, tid, unit);
+    stage_load<BITS, NT>(sr, a, tile(2), tile(0), tid);
     __syncthreads();
-    for (int i = threadIdx.x; i < kVBytes / 16; i += kThreads)
+    for (int i = tid; i < kVBytes / 16; i += NT)
       reinterpret_cast<v4u*>(sm.q.vb[1].v)[i] = v4u{0u, 0u, 0u, 0u};
     KFrag<FMT> kf;
     read_kfrag<FMT>(kf, sm.q.kb[0], col, half);
@@ -985,18 +1066,18 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
 #pragma unroll
       for (int e = 0; e < 8; ++e) pa[i][e] = pb[i][e] = (_Float16)0.0f;
     int c = 0;
-    for (; c + 3 < nq_tiles; c += 4) {
-      segA_tile<BITS, FMT, 0>(sm, a, c, qf, st, pa, pb, sr, kf);
-      segA_tile<BITS, FMT, 1>(sm, a, c + 1, qf, st, pb, pa, sr, kf);
-      segA_tile<BITS, FMT, 2>(sm, a, c + 2, qf, st, pa, pb, sr, kf);
-      segA_tile<BITS, FMT, 3>(sm, a, c + 3, qf, st, pb, pa, sr, kf);
+    for (; c + 3 < steps; c += 4) {
+      segA_tile<BITS, FMT, NT, S, 0>(sm, a, c, qf, st, pa, pb, sr, kf);
+      segA_tile<BITS, FMT, NT, S, 1>(sm, a, c + 1, qf, st, pb, pa, sr, kf);
+      segA_tile<BITS, FMT, NT, S, 2>(sm, a, c + 2, qf, st, pa, pb, sr, kf);
+      segA_tile<BITS, FMT, NT, S, 3>(sm, a, c + 3, qf, st, pb, pa, sr, kf);
     }
-    if (c < nq_tiles) segA_tile<BITS, FMT, 0>(sm, a, c, qf, st, pa, pb, sr, kf);
-    if (c + 1 < nq_tiles) segA_tile<BITS, FMT, 1>(sm, a, c + 1, qf, st, pb, pa, sr, kf);
-    if (c + 2 < nq_tiles) segA_tile<BITS, FMT, 2>(sm, a, c + 2, qf, st, pa, pb, sr, kf);
+    if (c < steps) segA_tile<BITS, FMT, NT, S, 0>(sm, a, c, qf, st, pa, pb, sr, kf);
+    if (c + 1 < steps) segA_tile<BITS, FMT, NT, S, 1>(sm, a, c + 1, qf, st, pb, pa, sr, kf);
+    if (c + 2 < steps) segA_tile<BITS, FMT, NT, S, 2>(sm, a, c + 2, qf, st, pa, pb, sr, kf);
     // P V of the last tile
-    const v8h (&plast)[4] = (nq_tiles & 1) ? pb : pa;
-    const VBuf& lb = sm.q.vb[(nq_tiles - 1) & 1];
+    const v8h (&plast)[4] = (steps & 1) ? pb : pa;
+    const VBuf& lb = sm.q.vb[(steps - 1) & 1];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
@@ -1017,31 +1098,23 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
       for (int ks = 0; ks < 8; ++ks) qb[ks] = *reinterpret_cast<const v8bf*>(qrow + ks * 16 + half * 8);
     }
     const int nft = (fp_count + kTile - 1) / kTile;
-    FpList fl;
-    fl.vl = vl;
-    fl.kq = kq_pos + (size_t)bj * n_kvblk * kTile;
-    fl.dummy = reinterpret_cast<const int32_t*>(Kh);
-    fl.nvl = nvl;
-    fl.nq0 = nq0;
-    fl.nqb = nqb;
-    fl.base = fp_base;
-    fl.count = fp_count;
-    fl.band_w = shift;
+    const FpList fl = fp_list(pl, vl, kq_pos + (size_t)bj * n_kvblk * kTile, Kh);
     // prologue: tile 0 published, tile 1 in registers.  Tile f is computed
     // from sm.f[f % 2] while tile f+1 (loaded during tile f-1) is written to
     // the other buffer and the rows of tile f+2 (and the position words of
     // tile f+3) are loaded; one barrier per tile.  Tiles past the end are
     // staged as padding into the free buffer (no branch).
-    if (threadIdx.x == 0) sm.f[0].ovf = sm.f[1].ovf = -1;
-    FpRegs fr;
-    fp_load_words(fr, fl, 0);
-    fp_load(fr, fl, Kh, Vh, 0, L);
+    if (group_tid<NT>() == 0) sm.f[0].ovf = sm.f[1].ovf = -1;
+    FpRegs<NT> fr;
+    fp_load_words<NT>(fr, fl, grp);
+    fp_load<NT, S>(fr, fl, Kh, Vh, grp, L);
     __syncthreads();
-    fp_store(sm.f[0], fr, inv_vref, 0, L);
-    fp_load(fr, fl, Kh, Vh, 1, L);
+    fp_store<NT>(sm.f[0], fr, inv_vref, grp, L);
+    fp_load<NT, S>(fr, fl, Kh, Vh, S + grp, L);
     __syncthreads();
-    for (int ft = 0; ft < nft; ++ft) {
-      FBuf& cur = sm.f[ft & 1];
+    for (int f = 0; f * S < nft; ++f) {   // the group's tile ft (all padding past the end)
+      const int ft = f * S + grp;
+      FBuf& cur = sm.f[f & 1];
       // without the band the list is ascending: a tile whose last position
       // is at or before the wave's first row is seen whole by every row
       const bool full = shift == 0 && cur.pos[kTile - 1] <= t0;
@@ -1050,9 +1123,13 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
       {
         // V of this tile outside the f16 range at the current sVref: raise
         // sVref to 2^(E - 134) (every |V| / sVref of the tile below 2^8),
-        // rescale the accumulator (exact), restage the tile's V
+        // rescale the accumulator (exact), restage the tile's V.  The barrier
+        // is for both groups, whichever has such a tile.
         const int ov = cur.ovf;
-        if ((ov >> 8) == ft) {
+        const bool mine = (ov >> 8) == ft;
+        const bool any = S == 1 ? mine
+                                : mine || (sms[S - 1 - grp].f[f & 1].ovf >> 8) == f * S + (S - 1 - grp);
+        if (mine) {
           const int ex = max(-100, (ov & 0xff) - 134);
           const float nv = fmaxf(vref, __builtin_ldexpf(1.0f, ex));
           const float c = vref / nv;
@@ -1062,9 +1139,9 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
             for (int r = 0; r < 16; ++r) st.acc[dg][r] *= c;
           vref = nv;
           inv_vref = 1.0f / nv;
-          fp_restage_v(cur, Vh, L, inv_vref);
-          __syncthreads();
+          fp_restage_v<NT>(cur, Vh, L, inv_vref);
         }
+        if (any) __syncthreads();
       }
       v16f sf[2];
 #pragma unroll
@@ -1078,8 +1155,8 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
           sf[kh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[ks], sf[kh], 0, 0, 0);
         }
       }
-      fp_store(sm.f[(ft + 1) & 1], fr, inv_vref, ft + 1, L);
-      fp_load(fr, fl, Kh, Vh, ft + 2, L);
+      fp_store<NT>(sm.f[(f + 1) & 1], fr, inv_vref, ft + S, L);
+      fp_load<NT, S>(fr, fl, Kh, Vh, ft + 2 * S, L);
       if (!full) {
 #pragma unroll
         for (int kh = 0; kh < 2; ++kh)
@@ -1102,6 +1179,37 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
     }
   }
 
+  if constexpr (S == 2) {
+    // the second group's state joins the first's (same units, same lanes)
+    struct Merge {
+      float acc[NW][64][64], m[NT], l[NT], vref[NT];
+    };
+    static_assert(sizeof(Merge) <= sizeof(sms), "the states fit the tiles' LDS");
+    Merge& mg = *reinterpret_cast<Merge*>(sms);
+    const int tid = group_tid<NT>();
+    if (grp == 1) {   // (every wave is past the last barrier of the tiles)
+#pragma unroll
+      for (int dg = 0; dg < 4; ++dg)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mg.acc[w][dg * 16 + r][lane] = st.acc[dg][r];
+      mg.m[tid] = st.m;
+      mg.l[tid] = st.l;
+      mg.vref[tid] = vref;
+    }
+    __syncthreads();
+    if (grp == 1) return;
+    const float M = fmaxf(st.m, mg.m[tid]);
+    const float f0 = __builtin_amdgcn_exp2f(st.m - M), f1 = __builtin_amdgcn_exp2f(mg.m[tid] - M);
+    const float c0 = f0 * vref, c1 = f1 * mg.vref[tid];
+#pragma unroll
+    for (int dg = 0; dg < 4; ++dg)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        st.acc[dg][r] = __builtin_fmaf(mg.acc[w][dg * 16 + r][lane], c1, st.acc[dg][r] * c0);
+    st.l = __builtin_fmaf(mg.l[tid], f1, st.l * f0);
+    vref = 1.0f;
+  }
+
   // ---------------- finalize: O = acc * sVref / l ----------------
   const float ltot = xhalf_sum(st.l);
   const float sc = vref / ltot;
@@ -1112,21 +1220,441 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
       const int d = dg * 32 + r4 * 8 + half * 4;
-      const float o0 = st.acc[dg][r4 * 4 + 0] * sc, o1 = st.acc[dg][r4 * 4 + 1] * sc;
-      const float o2 = st.acc[dg][r4 * 4 + 2] * sc, o3 = st.acc[dg][r4 * 4 + 3] * sc;
-      if (OUT_BF16) {
-        uint16_t* o = reinterpret_cast<uint16_t*>(out) + obase + d;
-        const __bf16 b0 = (__bf16)o0, b1 = (__bf16)o1, b2 = (__bf16)o2, b3 = (__bf16)o3;
-        const uint32_t w0 = (uint32_t)__builtin_bit_cast(uint16_t, b0) |
-                            ((uint32_t)__builtin_bit_cast(uint16_t, b1) << 16);
-        const uint32_t w1 = (uint32_t)__builtin_bit_cast(uint16_t, b2) |
-                            ((uint32_t)__builtin_bit_cast(uint16_t, b3) << 16);
-        *reinterpret_cast<uint2*>(o) = make_uint2(w0, w1);
-      } else {
-        float* o = reinterpret_cast<float*>(out) + obase + d;
-        *reinterpret_cast<float4*>(o) = make_float4(o0, o1, o2, o3);
+      store_out4<OUT_BF16>(out, obase + d, st.acc[dg][r4 * 4 + 0] * sc, st.acc[dg][r4 * 4 + 1] * sc,
+                           st.acc[dg][r4 * 4 + 2] * sc, st.acc[dg][r4 * 4 + 3] * sc);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Key-split variant for launches with too few work units to fill the chip:
+// one workgroup per unit, its 8 waves taking every 8th quantized tile and
+// every 8th full-precision tile, each with its own online-softmax state, and
+// merging the 8 states in LDS at the end.  A unit then takes about an eighth
+// of the serial steps.  The waves share no tile: K and V codes go from L2
+// straight into MFMA registers, a tile ahead, and no barrier couples the
+// waves; full-precision V tiles are transposed through a wave's own LDS.  The
+// price is that every wave converts its own V codes (160 vector instructions
+// a tile instead of 20), so full chips keep the shared-tile kernel.
+//
+// K rows are assigned to MFMA rows so that lane half h, register r of half-
+// tile kh holds key kh*32 + h*16 + r: a lane's 16 keys are contiguous, hence
+// its V operand is 16 contiguous codes of a channel.
+// ---------------------------------------------------------------------------
+constexpr int kSplitWaves = 8;
+constexpr int kAccPitch = kHeadDim + 4;   // floats per merged row (+4: bank shift)
+struct SplitTile {                        // a wave's full-precision tile
+  alignas(16) uint8_t v[kVBytes];
+  alignas(16) int32_t pos[kTile];
+  alignas(16) int32_t hi[kTile];
+};
+struct SplitMerge {
+  alignas(16) float acc[kSplitWaves][32 * kAccPitch];
+  float m[kSplitWaves][32], l[kSplitWaves][32], vref[kSplitWaves];
+};
+union SplitSmem {
+  SplitTile t[kSplitWaves];
+  SplitMerge mg;
+};
+
+// Key (of a 32-key half-tile) of MFMA row m.
+__device__ __forceinline__ int split_key(int m) {
+  return ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3);
+}
+
+// K and V codes of one tile in a wave's registers: the 16-byte chunks of K
+// row kh*32 + split_key(col) that make up this lane half's fragments, and of
+// V channel dg*32 + col the codes of keys kh*32 + half*16 .. +16.
+template <int BITS>
+struct SplitRaw {
+  static constexpr int kK = BITS == 8 ? 4 : 2;
+  v4u k[2][kK];
+  std::conditional_t<BITS == 8, v4u, v2u> v[4][2];
+};
+template <int BITS, int FMT>
+__device__ __forceinline__ void split_load_k(SplitRaw<BITS>& r, const uint8_t* kc, int col,
+                                             int half) {
+  constexpr int kRow = BITS == 8 ? kHeadDim : kHeadDim / 2;
+#pragma unroll
+  for (int kh = 0; kh < 2; ++kh) {
+    const v4u* row = reinterpret_cast<const v4u*>(kc + (kh * 32 + split_key(col)) * kRow);
+#pragma unroll
+    for (int i = 0; i < SplitRaw<BITS>::kK; ++i)
+      r.k[kh][i] = row[FMT == HYQ_FMT_FP8 ? (i >> 1) * 4 + half * 2 + (i & 1) : i * 2 + half];
+  }
+}
+template <int BITS>
+__device__ __forceinline__ void split_load_v(SplitRaw<BITS>& r, const uint8_t* vc, int col,
+                                             int half) {
+  constexpr int vRow = BITS == 8 ? kTile : kTile / 2;
+#pragma unroll
+  for (int dg = 0; dg < 4; ++dg)
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh) {
+      using T = std::remove_reference_t<decltype(r.v[dg][kh])>;
+      r.v[dg][kh] = *reinterpret_cast<const T*>(vc + (dg * 32 + col) * vRow + kh * (vRow / 2) +
+                                                half * (vRow / 4));
+    }
+}
+
+template <int BITS, int FMT>
+__device__ __forceinline__ void split_kfrag(KFrag<FMT>& kf, const SplitRaw<BITS>& r) {
+#pragma unroll
+  for (int kh = 0; kh < 2; ++kh) {
+    if constexpr (FMT == HYQ_FMT_FP8) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+        kf.f[kh][kk] = __builtin_shufflevector(__builtin_bit_cast(v4i, r.k[kh][2 * kk]),
+                                               __builtin_bit_cast(v4i, r.k[kh][2 * kk + 1]), 0, 1,
+                                               2, 3, 4, 5, 6, 7);
+    } else if constexpr (kv_fp4(FMT) || BITS == 8) {
+#pragma unroll
+      for (int i = 0; i < SplitRaw<BITS>::kK; ++i) kf.f[kh][i] = __builtin_bit_cast(v4i, r.k[kh][i]);
+    } else {   // a chunk of 32 int4 channels is two int8 fragments (16 * code)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        uint32_t o[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) i4x8_to_i8(r.k[kh][i][e], o[2 * e], o[2 * e + 1]);
+        kf.f[kh][2 * i] = v4i{(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
+        kf.f[kh][2 * i + 1] = v4i{(int)o[4], (int)o[5], (int)o[6], (int)o[7]};
       }
     }
+  }
+}
+// The Q fragments that go with split_kfrag: as read_qfrag, but int4 chunk i of
+// lane half h covers channels 64i + 32h .. +32, the fragments 2i and 2i + 1.
+template <int BITS, int FMT>
+__device__ __forceinline__ void split_qfrag(QFrag<FMT>& qf, const int8_t* qrow, bool ok, int half) {
+  if constexpr (BITS == 4 && FMT == HYQ_FMT_INT) {
+#pragma unroll
+    for (int k4 = 0; k4 < 4; ++k4)
+      qf.f[k4] = ok ? *reinterpret_cast<const v4i*>(qrow + (k4 >> 1) * 64 + half * 32 + (k4 & 1) * 16)
+                    : v4i{};
+  } else {
+    read_qfrag<FMT>(qf, qrow, ok, half);
+  }
+}
+
+// V operand of channel group dg: keys kh*32 + half*16 + 8*e .. +8 as f16 * 2^ev.
+template <int BITS, int FMT>
+__device__ __forceinline__ void split_vfrag(v8h (&va)[2], const SplitRaw<BITS>& r, int dg, int kh,
+                                            const VScale& vs) {
+  uint32_t h[8];
+  if constexpr (BITS == 8) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) codes4_to_h<FMT>(r.v[dg][kh][e], h[2 * e], h[2 * e + 1], vs);
+  } else if constexpr (kv_fp4(FMT)) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      e2m1x8_to_h(r.v[dg][kh][e], *reinterpret_cast<uint32_t(*)[4]>(&h[4 * e]), vs.f32);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      uint32_t b0, b1;
+      i4x8_to_i8(r.v[dg][kh][e], b0, b1);
+      i8x4_to_h(b0, h[4 * e], h[4 * e + 1], vs);
+      i8x4_to_h(b1, h[4 * e + 2], h[4 * e + 3], vs);
+    }
+  }
+  va[0] = __builtin_bit_cast(v8h, v4u{h[0], h[1], h[2], h[3]});
+  va[1] = __builtin_bit_cast(v8h, v4u{h[4], h[5], h[6], h[7]});
+}
+
+__device__ __forceinline__ float lane_max(const float (&s)[2][16]) {
+  float mx = -INFINITY;
+#pragma unroll
+  for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kh][r]);
+  return mx;
+}
+// Raise m to the tile maximum (of the lanes' maxima mx) when needed, then the
+// f16 weights 2^(s * c + log2 fm - m) into p and their sum, divided by fm,
+// into l (hidden keys are -inf; c > 0).
+__device__ __forceinline__ void split_softmax(NState& st, const float (&s)[2][16], float mx, float c,
+                                              float fm, v8h (&p)[4]) {
+  lazy_max(st, xhalf_max(mx) * c);
+  apply_corr(st);
+  const float bias = __builtin_amdgcn_logf(fm) - st.m;
+  const v2h one2 = {(_Float16)1.0f, (_Float16)1.0f};
+  float ps = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int kh = i >> 3, r = (i & 7) * 2;
+    v2f e;
+    e[0] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kh][r], c, bias));
+    e[1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kh][r + 1], c, bias));
+    const v2h pk = __builtin_convertvector(e, v2h);
+    ps = __builtin_amdgcn_fdot2(pk, one2, ps, false);
+    p[kh * 2 + (r >> 3)][r & 7] = pk[0];
+    p[kh * 2 + (r >> 3)][(r & 7) + 1] = pk[1];
+  }
+  st.l = __builtin_fmaf(ps, __builtin_amdgcn_rcpf(fm), st.l);
+}
+
+template <int BITS, int OUT_BF16, int FMT>
+__global__ void __launch_bounds__(kSplitWaves * 64, 1)
+attn_prefill_split_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+                          const uint16_t* __restrict__ V, const int32_t* __restrict__ idx,
+                          const int8_t* __restrict__ q_codes, const float* __restrict__ q_scale,
+                          const uint8_t* __restrict__ k_codes, const float* __restrict__ k_scale,
+                          const uint8_t* __restrict__ v_codes, const float* __restrict__ v_scale,
+                          const int32_t* __restrict__ kq_pos, void* __restrict__ out, int Hq,
+                          int Hkv, int nbj, int L, int P, int k, int nQ, int n_qblk, int n_kvblk,
+                          float alpha_log2e, int band_w) {
+  __shared__ SplitSmem sm;
+  const int g = Hq / Hkv;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int half = lane >> 5, col = lane & 31;
+  // unit u = (32-row block u / g, head u % g of the group), longest first
+  const int units = g * ((L + 31) / 32);
+  const int u = units - 1 - (int)blockIdx.x / nbj, bj = (int)blockIdx.x % nbj;
+  const int t0 = (u / g) * 32, t_last = min(L - 1, t0 + 31);
+  const int b = bj / Hkv, h = (bj % Hkv) * g + u % g;
+  const size_t bh = (size_t)b * Hq + h;
+  const int tq = t0 + col;
+  const bool row_ok = tq < L;
+  const uint16_t* Kh = K + (size_t)bj * L * kHeadDim;
+  const uint16_t* Vh = V + (size_t)bj * L * kHeadDim;
+  const int32_t* vl = idx + (size_t)bj * k;
+  const int32_t* kq0 = kq_pos + (size_t)bj * n_kvblk * kTile;
+
+  NState st;
+  init_state(st);
+  constexpr int kQBits = BITS == 16 ? 8 : BITS;   // (the quantized part compiles to nothing at 16)
+  constexpr size_t kTileK = (size_t)kTile * (kQBits == 8 ? kHeadDim : kHeadDim / 2);
+  constexpr size_t kTileV = (size_t)kHeadDim * (kQBits == 8 ? kTile : kTile / 2);
+  const uint8_t* kc0 = BITS == 16 ? nullptr : k_codes + (size_t)bj * n_kvblk * kTileK;
+  const uint8_t* vc0 = BITS == 16 ? nullptr : v_codes + (size_t)bj * n_kvblk * kTileV;
+  SplitRaw<kQBits> raw;
+  QFrag<FMT> qf;
+  if (BITS != 16 && n_kvblk > 0) {   // the first tile, in flight during the searches
+    const int c = min(w, n_kvblk - 1);
+    split_load_k<kQBits, FMT>(raw, kc0 + c * kTileK, col, half);
+    split_qfrag<kQBits, FMT>(qf, q_codes + (bh * L + (row_ok ? tq : 0)) * kHeadDim, row_ok, half);
+    split_load_v<kQBits>(raw, vc0 + c * kTileV, col, half);
+  }
+  const KeyPlan pl = key_plan<BITS, FMT>(vl, v_scale + (size_t)bj * n_kvblk, k, P, nQ, n_kvblk, t0,
+                                         t_last, band_w);
+  float vref = pl.vref, inv_vref = 1.0f / vref;
+
+  // ---------------- quantized keys ----------------
+  if (BITS != 16) {
+    constexpr float kSub = (BITS == 8 || kv_fp4(FMT)) ? 1.0f : 0.0625f;
+    const float* ks0 = k_scale + (size_t)bj * n_kvblk;
+    const float* vs0 = v_scale + (size_t)bj * n_kvblk;
+    const float cq = alpha_log2e * q_scale[bh * n_qblk + t0 / kBlock];
+    const int last_seen = t0 - pl.shift;   // every row sees quantized positions up to here
+    for (int c = w; c < pl.nq_tiles; c += kSplitWaves) {
+      const int cn = min(c + kSplitWaves, pl.nq_tiles - 1);   // past the end: loaded, not used
+      const float sv = vs0[c] * kSub;
+      // (a zero K block has zero scores: the floor keeps -inf * c from a NaN)
+      const float cqk = fmaxf(cq * (ks0[c] * kSub), 1e-30f);
+      int ev;
+      float fm = __builtin_frexpf(sv * inv_vref, &ev);
+      if (!(sv > 0.0f)) {   // all-zero V block: its V codes are 0, fold nothing
+        fm = 1.0f;
+        ev = 0;
+      }
+      const VScale vs = make_vscale(__builtin_ldexpf(1.0f, ev));
+      const bool diag = kq0[c * kTile + kTile - 1] > last_seen;
+      SVec<FMT> s[2];
+      {
+        KFrag<FMT> kf;
+        split_kfrag<kQBits, FMT>(kf, raw);
+        qk_tile<FMT>(s, kf, qf);
+      }
+      split_load_k<kQBits, FMT>(raw, kc0 + cn * kTileK, col, half);
+      float y[2][16];
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) y[kh][r] = (float)s[kh][r];
+      // the maximum first: its reads of the MFMA results stay on the straight
+      // path, where the compiler pads them with the wait states they need
+      float mx = lane_max(y);
+      asm volatile("" : "+v"(mx));   // (keeps it there)
+      if (diag) {
+        const int tv = tq - pl.shift;
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            const v4i p4 = *reinterpret_cast<const v4i*>(kq0 + c * kTile + kh * 32 + half * 16 + r4 * 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              y[kh][r4 * 4 + j] = p4[j] <= tv ? y[kh][r4 * 4 + j] : -INFINITY;
+          }
+        mx = lane_max(y);
+      }
+      v8h p[4];
+      split_softmax(st, y, mx, cqk, fm, p);
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+        for (int dg = 0; dg < 4; ++dg) {
+          v8h va[2];
+          split_vfrag<kQBits, FMT>(va, raw, dg, kh, vs);
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+            st.acc[dg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[e], p[kh * 2 + e], st.acc[dg], 0,
+                                                                0, 0);
+        }
+      split_load_v<kQBits>(raw, vc0 + cn * kTileV, col, half);
+    }
+  }
+
+  // ---------------- full-precision keys ----------------
+  const int nft = (pl.fp_count + kTile - 1) / kTile;
+  if (w < nft) {
+    SplitTile& T = sm.t[w];
+    v8bf qb[8];
+    const uint16_t* qrow = Q + (bh * L + (row_ok ? tq : 0)) * kHeadDim;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qb[ks] = *reinterpret_cast<const v8bf*>(qrow + ks * 16 + half * 8);
+    const FpList fl = fp_list(pl, vl, kq0, Kh);
+    for (int ft = w; ft < nft; ft += kSplitWaves) {
+      // K rows of this lane's two MFMA rows; V rows of key pair `col`
+      int pk[2], hk[2], pv[2], hv[2];
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh) {
+        const int e = ft * kTile + kh * 32 + split_key(col);
+        fp_resolve(fl, e, *fp_src(fl, e), pk[kh], hk[kh]);
+        const int ev = ft * kTile + 2 * col + kh;
+        fp_resolve(fl, ev, *fp_src(fl, ev), pv[kh], hv[kh]);
+      }
+      v4u kr[2][8];
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh) {   // padding rows read row 0; they are hidden below
+        const size_t row = (unsigned)pk[kh] < (unsigned)L ? (size_t)pk[kh] : 0;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+          kr[kh][ks] = reinterpret_cast<const v4u*>(Kh + row * kHeadDim)[ks * 2 + half];
+      }
+      if (half == 0) {
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh) {
+          T.pos[kh * 32 + split_key(col)] = pk[kh];
+          T.hi[kh * 32 + split_key(col)] = hk[kh];
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      v16f sf[2];
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sf[kh][r] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+          sf[kh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, kr[kh][ks]), qb[ks],
+                                                           sf[kh], 0, 0, 0);
+      }
+      // V: pair `col`, chunks 2i + half
+      v4u vr[2][8];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const bool ok = (unsigned)pv[x] < (unsigned)L;
+        const size_t row = ok ? (size_t)pv[x] : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          vr[x][i] = reinterpret_cast<const v4u*>(Vh + row * kHeadDim)[2 * i + half] &
+                     (ok ? 0xffffffffu : 0u);
+      }
+      const bool full = pl.shift == 0 && T.pos[kTile - 1] <= t0;
+      if (!full) {
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            const int e = kh * 32 + half * 16 + r4 * 4;
+            const v4i p4 = *reinterpret_cast<const v4i*>(&T.pos[e]);
+            const v4i h4 = *reinterpret_cast<const v4i*>(&T.hi[e]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              sf[kh][r4 * 4 + j] =
+                  ((p4[j] <= tq) & (tq <= h4[j])) ? sf[kh][r4 * 4 + j] : -INFINITY;
+          }
+      }
+      v8h p[4];
+      fp_softmax(st, sf, alpha_log2e, p);
+      float mx = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        mx = fmaxf(mx, fp_store_vpair(T.v, vr[0][i], vr[1][i], 2 * col, 2 * i + half, inv_vref));
+      if (__ballot(!(mx * inv_vref <= 65504.0f) && mx == mx)) {
+        // V outside the f16 range at the current sVref: raise it to 2^(E - 134)
+        // (every |V| / sVref of the tile below 2^8), rescale, store again
+        int ex = (int)(__float_as_uint(mx) >> 23);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) ex = max(ex, __shfl_xor(ex, o, 64));
+        const float nv = fmaxf(vref, __builtin_ldexpf(1.0f, max(-100, ex - 134)));
+        const float c = vref / nv;
+#pragma unroll
+        for (int dg = 0; dg < 4; ++dg)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) st.acc[dg][r] *= c;
+        vref = nv;
+        inv_vref = 1.0f / nv;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          fp_store_vpair(T.v, vr[0][i], vr[1][i], 2 * col, 2 * i + half, inv_vref);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int dg = 0; dg < 4; ++dg) {
+          const v8h va = *reinterpret_cast<const v8h*>(T.v + (dg * 32 + col) * kVPitch +
+                                                       (ks >> 1) * 64 + half * 32 + (ks & 1) * 16);
+          st.acc[dg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va, p[ks], st.acc[dg], 0, 0, 0);
+        }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  }
+
+  // ---------------- merge of the 8 states ----------------
+  const float lw = xhalf_sum(st.l);
+  __syncthreads();   // the tiles' LDS is reused
+  SplitMerge& mg = sm.mg;
+#pragma unroll
+  for (int dg = 0; dg < 4; ++dg)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4)
+      *reinterpret_cast<float4*>(&mg.acc[w][col * kAccPitch + dg * 32 + r4 * 8 + half * 4]) =
+          make_float4(st.acc[dg][r4 * 4], st.acc[dg][r4 * 4 + 1], st.acc[dg][r4 * 4 + 2],
+                      st.acc[dg][r4 * 4 + 3]);
+  if (half == 0) {
+    mg.m[w][col] = st.m;
+    mg.l[w][col] = lw;
+  }
+  if (lane == 0) mg.vref[w] = vref;
+  __syncthreads();
+  const int row = (int)threadIdx.x >> 4, d0 = ((int)threadIdx.x & 15) * 8;
+  float M = mg.m[0][row];
+#pragma unroll
+  for (int v = 1; v < kSplitWaves; ++v) M = fmaxf(M, mg.m[v][row]);
+  float l = 0.0f, o[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = 0.0f;
+#pragma unroll
+  for (int v = 0; v < kSplitWaves; ++v) {
+    const float f = __builtin_amdgcn_exp2f(mg.m[v][row] - M), fv = f * mg.vref[v];
+    l = __builtin_fmaf(mg.l[v][row], f, l);
+#pragma unroll
+    for (int e4 = 0; e4 < 2; ++e4) {
+      const float4 a = *reinterpret_cast<const float4*>(&mg.acc[v][row * kAccPitch + d0 + e4 * 4]);
+      o[e4 * 4 + 0] = __builtin_fmaf(a.x, fv, o[e4 * 4 + 0]);
+      o[e4 * 4 + 1] = __builtin_fmaf(a.y, fv, o[e4 * 4 + 1]);
+      o[e4 * 4 + 2] = __builtin_fmaf(a.z, fv, o[e4 * 4 + 2]);
+      o[e4 * 4 + 3] = __builtin_fmaf(a.w, fv, o[e4 * 4 + 3]);
+    }
+  }
+  if (t0 + row >= L) return;
+  const float sc = 1.0f / l;
+  const size_t at = (bh * L + t0 + row) * kHeadDim + d0;
+  store_out4<OUT_BF16>(out, at, o[0] * sc, o[1] * sc, o[2] * sc, o[3] * sc);
+  store_out4<OUT_BF16>(out, at + 4, o[4] * sc, o[5] * sc, o[6] * sc, o[7] * sc);
 }
 
 template <int BITS, int OB, int FMT>
@@ -1135,15 +1663,31 @@ hipError_t launch_t(const hyq_shape& s, const hyq_sizes& z, const uint16_t* Q,
                     const int8_t* q_codes, const float* q_scale, const uint8_t* k_codes,
                     const float* k_scale, const uint8_t* v_codes, const float* v_scale,
                     const int32_t* kq_pos, float softmax_scale, void* out, hipStream_t st) {
-  const int g = s.Hq / s.Hkv;
-  const int nrb = (s.L + 31) / 32;
-  const int wg_per_bj = (g * nrb + kWaves - 1) / kWaves;
+  const int units = s.Hq / s.Hkv * ((s.L + 31) / 32);   // per KV head
   const int nbj = s.B * s.Hkv;
-  const dim3 grid(wg_per_bj * nbj);
-  attn_prefill_kernel<BITS, OB, FMT><<<grid, kThreads, 0, st>>>(
-      Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes, v_scale, kq_pos, out, s.Hq,
-      s.Hkv, nbj, s.L, z.P, z.k, z.nQ, z.n_qblk, z.n_kvblk, softmax_scale * kLog2e,
-      s.window_mode == HYQ_WIN_BAND ? s.window : 0);
+  const int band_w = s.window_mode == HYQ_WIN_BAND ? s.window : 0;
+#define HYQ_ARGS                                                                              \
+  Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes, v_scale, kq_pos, out, s.Hq, s.Hkv, \
+      nbj, s.L, z.P, z.k, z.nQ, z.n_qblk, z.n_kvblk, softmax_scale * kLog2e, band_w
+  const AttnShape sh = choose_attn_shape(units, nbj, (s.L + kTile - 1) / kTile, BITS == 16,
+                                         device_cus());
+  const int n = (int)(sh.grid / nbj);   // workgroups per KV head
+  const dim3 grid((unsigned)sh.grid);
+  switch (sh.kind) {
+    case AttnKind::kSplit8:
+      attn_prefill_split_kernel<BITS, OB, FMT><<<grid, kSplitWaves * 64, 0, st>>>(HYQ_ARGS);
+      break;
+    case AttnKind::kSplit2:
+      attn_prefill_kernel<BITS, OB, FMT, 4, 2><<<grid, 512, 0, st>>>(HYQ_ARGS, n);
+      break;
+    case AttnKind::kHalf:   // two resident workgroups per CU
+      attn_prefill_kernel<BITS, OB, FMT, 4, 1><<<grid, 256, 0, st>>>(HYQ_ARGS, sh.fold);
+      break;
+    case AttnKind::kFull:
+      attn_prefill_kernel<BITS, OB, FMT, 8, 1><<<grid, 512, 0, st>>>(HYQ_ARGS, n);
+      break;
+  }
+#undef HYQ_ARGS
   return hipGetLastError();
 }
 

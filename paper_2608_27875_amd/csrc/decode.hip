@@ -745,7 +745,6 @@ decode_combine_kernel(const float* __restrict__ part, void* __restrict__ out, in
 
 // ---- host launchers -------------------------------------------------------
 
-// Compute units of the current device (cached per device).
 // Scratch of hyq_decode_attn_noalloc: the split partials of one launch, in
 // a file-scope device array (each GPU holds its own copy at its own address,
 // from the first use of the library on it until the process ends).  Host
@@ -775,7 +774,7 @@ hipError_t noalloc_scratch(float** out) {
   return hipSuccess;
 }
 
-static int device_cus() {
+int device_cus() {
   constexpr int kMaxDev = 64;
   static std::atomic<int> cus[kMaxDev];
   int dev = 0;

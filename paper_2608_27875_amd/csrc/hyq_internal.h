@@ -12,6 +12,9 @@ namespace hyq {
 
 // ---- host-side launch wrappers (each returns a hipError_t) ----------------
 
+// Compute units of the current device (cached per device).
+int device_cus();
+
 // The Q blocks of a call (64 rows of one head each), head-major.
 struct QuantQ {
   const uint16_t* Q;

@@ -1,0 +1,73 @@
+"""The prefill attention's launch shapes (attn_shape.h; the sizes below take
+each of them on 256 CUs) against the oracle: every code format, ragged
+lengths whose last tile and last workgroup are partial, the per-query window,
+and full-precision V beyond the f16 range (each key group raises its own
+reference scale before the groups are merged)."""
+import numpy as np
+import pytest
+
+import gpu_common as gc
+from oracle import hyq_oracle as orc
+from paper_2608_27875_amd import gen
+
+hyq = gc.hyq
+pytestmark = pytest.mark.gpu
+
+# kind: (B, Hq, Hkv, L); 32-row units in all -> split8: 5, 175; split2: 616;
+# half: 1520; full: 2528
+SHAPES = {"split8_tiny": (1, 1, 1, 131), "split8": (1, 5, 1, 1111), "split2": (2, 14, 2, 703),
+          "half": (1, 40, 8, 1201), "full": (1, 32, 8, 2501)}
+FORMATS = {"int8": (8, hyq.FMT_INT), "int4": (4, hyq.FMT_INT), "fp8": (8, hyq.FMT_FP8),
+           "fp4": (4, hyq.FMT_FP4), "fp4q6": (4, hyq.FMT_FP4Q6), "bf16": (16, hyq.FMT_INT)}
+
+
+def _run(kind, fmt, W, band=False, big_v=()):
+    B, Hq, Hkv, L = SHAPES[kind]
+    bits, f = FORMATS[fmt]
+    d = gen.generate(5, 500 + L, B=B, Hq=Hq, Hkv=Hkv, L=L, D=128, W=W, plant=0.03)
+    if big_v:
+        x = gen.bf16_bits_to_f32(d["V"])
+        for pos, ch, v in big_v:
+            x[..., pos, ch] = v
+        d["V"] = gen.f32_to_bf16_bits(x)
+    shape = hyq.Shape(B=B, Hq=Hq, Hkv=Hkv, L=L, window=W, budget_ppm=50000, bits_kv=bits,
+                      kv_format=f, window_mode=hyq.WIN_BAND if band else hyq.WIN_FIXED)
+    t = tuple(gc.to_dev(d[n]) for n in ("Q", "K", "V"))
+    b = hyq.alloc_buffers(shape, t[0].device)
+    out = hyq.prefill(shape, *t, b).cpu().numpy()
+    idx, _ = orc.select_vertical(d["Q"], d["K"], Hkv, W, 50000)
+    np.testing.assert_array_equal(b["idx"].cpu().numpy(), idx)
+    qz = orc.quantize(d["Q"], d["K"], d["V"], idx, W, bits,
+                      fmt=gc.fmt_name(shape) if bits != 16 else "int")
+    heads = [(0, 0), (B - 1, Hq - 1)] if Hq > 1 else [(0, 0)]
+    rows = gc.sample_rows(L, W, 70, 1)
+    rows = np.union1d(rows, [31, 32, 63, 64, 65, min(L - 1, 700)])
+    O = orc.attention(d["Q"], d["K"], d["V"], W, bits, idx, qz, heads=heads, rows=rows,
+                      window_mode="band" if band else "fixed")
+    return np.stack([out[bb, h][rows] for bb, h in heads]), O
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+@pytest.mark.parametrize("kind", SHAPES)
+def test_shapes(kind, fmt):
+    G, O = _run(kind, fmt, W=100)
+    mx, mean = gc.attention_error(G, O)
+    assert mx <= gc.TOL_MAX and mean <= gc.TOL_MEAN, (mx, mean)
+
+
+@pytest.mark.parametrize("fmt", ["int8", "fp4q6"])
+@pytest.mark.parametrize("kind", SHAPES)
+def test_band(kind, fmt):
+    G, O = _run(kind, fmt, W=90, band=True)
+    mx, mean = gc.attention_error(G, O)
+    assert mx <= gc.TOL_MAX and mean <= gc.TOL_MEAN, (mx, mean)
+
+
+@pytest.mark.parametrize("fmt", ["int8", "bf16"])
+@pytest.mark.parametrize("kind", ["split8", "split2", "half", "full"])
+def test_v_beyond_f16(kind, fmt):
+    L = SHAPES[kind][3]
+    G, O = _run(kind, fmt, W=200, big_v=[(L - 170, 7, 1.0e5), (L - 60, 20, -3.0e6)])
+    keep = ~np.isin(np.arange(128), [7, 20])
+    mx, mean = gc.attention_error(G[..., keep], O[..., keep])
+    assert gc.scaled_error(G, O) <= gc.TOL_MAX and mx <= gc.TOL_MAX and mean <= gc.TOL_MEAN
