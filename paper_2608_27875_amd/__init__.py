@@ -14,6 +14,7 @@ from __future__ import annotations
 
 import ctypes
 import dataclasses
+import functools
 import math
 import os
 
@@ -135,10 +136,26 @@ def _check(rc: int):
         raise HyqError(rc, lib().hyq_last_error().decode() or lib().hyq_strerror(rc).decode())
 
 
+def _derive(shape: Shape):
+    c, z = shape.c(), _Sizes()
+    _check(lib().hyq_sizes_for(ctypes.byref(c), ctypes.byref(z)))
+    return c, {n: getattr(z, n) for n, _ in _Sizes._fields_}
+
+
+# Pure functions of the shape's values (a frozen dataclass), which programs
+# pass again on every call: the struct (only ever read) and the sizes.
+_derived_by_value = functools.lru_cache(maxsize=256)(_derive)
+
+
+def _derived(shape: Shape):
+    try:
+        return _derived_by_value(shape)
+    except TypeError:      # a field of an unhashable integer-like type
+        return _derive(shape)
+
+
 def hyq_sizes_for(shape: Shape) -> dict:
-    z = _Sizes()
-    _check(lib().hyq_sizes_for(ctypes.byref(shape.c()), ctypes.byref(z)))
-    return {n: getattr(z, n) for n, _ in _Sizes._fields_}
+    return dict(_derived(shape)[1])
 
 
 def hyq_strerror(code: int) -> str:
@@ -153,6 +170,7 @@ def hyq_last_error() -> str:
 # argument marshalling
 # --------------------------------------------------------------------------
 
+@functools.lru_cache(maxsize=None)
 def _torch():
     import torch
     return torch
@@ -160,9 +178,9 @@ def _torch():
 
 def _stream(stream):
     torch = _torch()
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    if stream is None:   # the current stream of the current device
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ptr(t, name, nbytes, dtypes, device, allow_none=False):
@@ -177,10 +195,11 @@ def _ptr(t, name, nbytes, dtypes, device, allow_none=False):
         raise ValueError(f"{name} is on {t.device}, expected {device}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    have = t.numel() * t.element_size()
+    n = t.numel()
+    have = n * t.element_size()
     if have < nbytes:
         raise ValueError(f"{name} holds {have} bytes, needs {nbytes}")
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else None
+    return t.data_ptr() if n else None
 
 
 def _io(shape: Shape, Q, K, V=None):
@@ -202,7 +221,7 @@ def _io(shape: Shape, Q, K, V=None):
 def hyq_select_vertical(shape: Shape, Q, K, idx, scores=None, ws=None, stream=None):
     """Algorithm 1 (see include/hyq.h); writes idx [B,Hkv,k] (and scores)."""
     torch = _torch()
-    z = hyq_sizes_for(shape)
+    sc, z = _derived(shape)
     dev, bf = _io(shape, Q, K)
     args = [
         _ptr(Q, "Q", Q.numel() * 2, bf, dev),
@@ -212,15 +231,15 @@ def hyq_select_vertical(shape: Shape, Q, K, idx, scores=None, ws=None, stream=No
         _ptr(ws, "ws", z["select_ws_bytes"], (torch.uint8, torch.int8, torch.float32), dev),
     ]
     wsb = 0 if ws is None else ws.numel() * ws.element_size()
-    _check(lib().hyq_select_vertical(ctypes.byref(shape.c()), args[0], args[1], args[2], args[3],
-                                     args[4], ctypes.c_size_t(wsb), _stream(stream)))
+    _check(lib().hyq_select_vertical(ctypes.byref(sc), args[0], args[1], args[2], args[3],
+                                     args[4], wsb, _stream(stream)))
 
 
 def hyq_quantize(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes,
                  v_scale, kq_pos, stream=None):
     """Algorithm 2, Stages 1-2 (see include/hyq.h)."""
     torch = _torch()
-    z = hyq_sizes_for(shape)
+    sc, z = _derived(shape)
     if shape.bits_kv == 16:
         return
     dev, bf = _io(shape, Q, K, V)
@@ -239,14 +258,14 @@ def hyq_quantize(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale,
         _ptr(v_scale, "v_scale", z["kv_scale_bytes"], f32, dev),
         _ptr(kq_pos, "kq_pos", z["kq_pos_bytes"], i32, dev),
     ]
-    _check(lib().hyq_quantize(ctypes.byref(shape.c()), *a, _stream(stream)))
+    _check(lib().hyq_quantize(ctypes.byref(sc), *a, _stream(stream)))
 
 
 def hyq_attn_prefill(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes,
                      v_scale, kq_pos, softmax_scale, out, out_dtype=0, stream=None):
     """Algorithm 2, Stage 3 / eq. (prefill_hybrid) (see include/hyq.h)."""
     torch = _torch()
-    z = hyq_sizes_for(shape)
+    sc, z = _derived(shape)
     dev, bf = _io(shape, Q, K, V)
     u8 = (torch.uint8, torch.int8)
     f32 = (torch.float32,)
@@ -267,8 +286,8 @@ def hyq_attn_prefill(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_sc
         _ptr(kq_pos, "kq_pos", z["kq_pos_bytes"], i32, dev, allow_none=not quant),
     ]
     o = _ptr(out, "out", out_bytes, odt, dev)
-    _check(lib().hyq_attn_prefill(ctypes.byref(shape.c()), *a, ctypes.c_float(softmax_scale), o,
-                                  ctypes.c_int32(out_dtype), _stream(stream)))
+    _check(lib().hyq_attn_prefill(ctypes.byref(sc), *a, softmax_scale, o, out_dtype,
+                                  _stream(stream)))
 
 
 def hyq_prefill(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes,
@@ -276,7 +295,7 @@ def hyq_prefill(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, 
     """Algorithm 2 as one call: selection, quantization and attention
     (see include/hyq.h); the library checks all three before launching."""
     torch = _torch()
-    z = hyq_sizes_for(shape)
+    sc, z = _derived(shape)
     dev, bf = _io(shape, Q, K, V)
     u8 = (torch.uint8, torch.int8)
     f32 = (torch.float32,)
@@ -301,8 +320,8 @@ def hyq_prefill(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, 
     w = _ptr(ws, "ws", z["select_ws_bytes"], (torch.uint8, torch.int8, torch.float32), dev,
              allow_none=not sel)
     wsb = 0 if ws is None else ws.numel() * ws.element_size()
-    _check(lib().hyq_prefill(ctypes.byref(shape.c()), *a, ctypes.c_float(softmax_scale), o,
-                             ctypes.c_int32(out_dtype), w, ctypes.c_size_t(wsb), _stream(stream)))
+    _check(lib().hyq_prefill(ctypes.byref(sc), *a, softmax_scale, o, out_dtype, w, wsb,
+                             _stream(stream)))
 
 
 # --------------------------------------------------------------------------
@@ -312,7 +331,7 @@ def hyq_prefill(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, 
 def alloc_buffers(shape: Shape, device, out_dtype: int = 0) -> dict:
     """Every intermediate and output buffer of one prefill call (torch tensors)."""
     torch = _torch()
-    z = hyq_sizes_for(shape)
+    sc, z = _derived(shape)
 
     def u8(n):
         return torch.empty(max(n, 0), dtype=torch.uint8, device=device)
@@ -410,11 +429,11 @@ class DecodeCache:
 
 
 def _decode_rows_ok(cache: DecodeCache, t, name, heads):
-    torch = _torch()
-    want = (cache.c.B, heads, cache.c.D)
-    if tuple(t.shape) != want:
+    c = cache.c
+    want = (c.B, heads, c.D)
+    if t.shape != want:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {want}")
-    return _ptr(t, name, t.numel() * 2, (torch.bfloat16,), cache.device)
+    return _ptr(t, name, t.numel() * 2, (_torch().bfloat16,), cache.device)
 
 
 def hyq_freeze(shape: Shape, Q, K, V, cache: DecodeCache, stream=None):
@@ -425,9 +444,8 @@ def hyq_freeze(shape: Shape, Q, K, V, cache: DecodeCache, stream=None):
     a = [_ptr(Q, "Q", Q.numel() * 2, bf, dev), _ptr(K, "K", K.numel() * 2, bf, dev),
          _ptr(V, "V", V.numel() * 2, bf, dev)]
     ws = cache.freeze_ws
-    _check(lib().hyq_freeze(ctypes.byref(shape.c()), *a, ctypes.byref(cache.c),
-                            ctypes.c_void_p(ws.data_ptr()),
-                            ctypes.c_size_t(ws.numel()), _stream(stream)))
+    _check(lib().hyq_freeze(ctypes.byref(_derived(shape)[0]), *a, ctypes.byref(cache.c),
+                            ws.data_ptr(), ws.numel(), _stream(stream)))
 
 
 def hyq_decode_append(cache: DecodeCache, k_new, v_new, stream=None):
@@ -447,9 +465,8 @@ def hyq_decode_attn(cache: DecodeCache, q, out, softmax_scale: float | None = No
     nb = cache.c.B * cache.c.Hq * cache.c.D * (4 if out_dtype == 0 else 2)
     o = _ptr(out, "out", nb, odt, cache.device)
     ws = cache.attn_ws
-    _check(lib().hyq_decode_attn(ctypes.byref(cache.c), qp, ctypes.c_float(scale), o,
-                                 ctypes.c_int32(out_dtype), ctypes.c_void_p(ws.data_ptr()),
-                                 ctypes.c_size_t(ws.numel()), _stream(stream)))
+    _check(lib().hyq_decode_attn(ctypes.byref(cache.c), qp, scale, o, out_dtype, ws.data_ptr(),
+                                 ws.numel(), _stream(stream)))
 
 
 NOALLOC_SCRATCH_BYTES = 16 << 20   # HYQ_NOALLOC_SCRATCH_BYTES
@@ -465,5 +482,5 @@ def hyq_decode_attn_noalloc(cache: DecodeCache, q, out, softmax_scale: float | N
     odt = (torch.float32,) if out_dtype == 0 else (torch.bfloat16,)
     nb = cache.c.B * cache.c.Hq * cache.c.D * (4 if out_dtype == 0 else 2)
     o = _ptr(out, "out", nb, odt, cache.device)
-    _check(lib().hyq_decode_attn_noalloc(ctypes.byref(cache.c), qp, ctypes.c_float(scale), o,
-                                         ctypes.c_int32(out_dtype), _stream(stream)))
+    _check(lib().hyq_decode_attn_noalloc(ctypes.byref(cache.c), qp, scale, o, out_dtype,
+                                         _stream(stream)))
