@@ -127,11 +127,19 @@ struct FBuf {                       // one full-precision tile
   int32_t ovf;     // (f << 8) | E: tile f staged here had a V / sVref outside the f16
                    // range, E the largest biased float exponent of its V values
 };
+// Nothing quantized: tile c multiplies K(c) and V(c-1), as the quantized
+// segment does, while K(c+1) and V(c) are written.
+struct DRing {
+  alignas(16) uint8_t k[2][kTile * kKPitchBf];   // bf16 K rows
+  VBuf vb[2];                                    // V^T as f16 V / sVref
+  int32_t ovf[2];                                // as FBuf's, of the V tile beside it
+};
 // Full-precision tiles alternate between two buffers: tile f+1 is written
 // while tile f is computed.
 union Smem {
   QRing q;
   FBuf f[2];
+  DRing d;
 };
 
 __device__ __forceinline__ float xhalf_max(float x) {
@@ -871,6 +879,164 @@ __device__ __forceinline__ void segA_tile(Smem& sm, const SegA& a, int c, const 
   __syncthreads();
 }
 
+// ---------------------------------------------------------------------------
+// Every key in full precision (bits 16): consecutive rows, so no key list, and
+// the quantized segment's pipeline.  Tile c: S^T(c) with the bf16 MFMA; K(c+1)
+// and V(c) from registers to LDS (V converted to f16 V / sVref and transposed)
+// and the loads of K(c+2), V(c+1) in its shadow; then P V(c-1) interleaved
+// with the fast-path softmax of tile c.  One barrier per tile.  What bounds
+// it is the chip's power under matrix work, then vector instructions (about
+// 170 per tile and wave beside 32 MFMAs; the key-list stage, which computes
+// each row's position, tile maximum and visibility and runs its products and
+// its softmax one after the other, takes 296).  GQA 32q/8kv at 32k: 9.47 ms
+// with the key-list stage, 8.33 ms (1056 TFLOP/s) here; at 8k 622 and 549 us.
+// ---------------------------------------------------------------------------
+struct SegD {
+  const uint8_t* k0;
+  const uint8_t* v0;
+  int n, grp, L;
+  int t0;             // first query row of the wave
+  float alpha_log2e;
+  int half, col;
+};
+template <int NT>
+struct DenseRegs {
+  static constexpr int kK = kTile * 16 / NT, kV = (kTile / 2) * 16 / NT;
+  v4u k[kK], v[2 * kV];
+};
+// 16-byte chunk of a row of tile t (rows past L read the last one: hidden).
+__device__ __forceinline__ v4u dense_chunk(const uint8_t* base, int t, int key, int chunk, int L) {
+  const uint32_t row = (uint32_t)min(t * kTile + key, L - 1);
+  return *reinterpret_cast<const v4u*>(base + (size_t)(row * (uint32_t)(kHeadDim * 2) + chunk * 16));
+}
+template <int NT>
+__device__ __forceinline__ void dense_load_k(DenseRegs<NT>& r, const SegD& a, int t) {
+#pragma unroll
+  for (int i = 0; i < DenseRegs<NT>::kK; ++i)
+    r.k[i] = dense_chunk(a.k0, t, fp_kkey<NT>(i), (group_tid<NT>() + i * NT) & 15, a.L);
+}
+template <int NT>
+__device__ __forceinline__ void dense_load_v(DenseRegs<NT>& r, const SegD& a, int t) {
+#pragma unroll
+  for (int i = 0; i < DenseRegs<NT>::kV; ++i)
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      r.v[2 * i + x] = dense_chunk(a.v0, t, fp_vkey<NT>(i, x), fp_vchunk<NT>(i), a.L);
+}
+template <int NT>
+__device__ __forceinline__ void dense_store_k(uint8_t* kb, const DenseRegs<NT>& r) {
+#pragma unroll
+  for (int i = 0; i < DenseRegs<NT>::kK; ++i)
+    *reinterpret_cast<v4u*>(kb + fp_kkey<NT>(i) * kKPitchBf +
+                            ((group_tid<NT>() + i * NT) & 15) * 16) = r.k[i];
+}
+// V of tile t; a ratio outside the f16 range is recorded as fp_store does.
+template <int NT>
+__device__ __forceinline__ void dense_store_v(VBuf& vb, int32_t& ovf, const DenseRegs<NT>& r, int t,
+                                              float inv_vref) {
+  float mx = 0.0f;
+#pragma unroll
+  for (int i = 0; i < DenseRegs<NT>::kV; ++i)
+    mx = fmaxf(mx, fp_store_vpair(vb.v, r.v[2 * i], r.v[2 * i + 1], vslot(fp_vkey<NT>(i, 0)),
+                                  fp_vchunk<NT>(i), inv_vref));
+  if (!(mx * inv_vref <= 65504.0f)) atomicMax(&ovf, (t << 8) | (int)(__float_as_uint(mx) >> 23));
+}
+
+// V(c-1), staged one tile ago, outside the f16 range at the sVref of then:
+// raise sVref to 2^(E - 134) (every |V| / sVref of the tile below 2^8),
+// rescale the accumulator (exact) and stage that tile's V again (also for the
+// last tile that an all-hidden step staged in its place: its zero weights must
+// not meet an infinity).  Uniform over the workgroup; with S = 2 the barrier
+// is for both groups.
+template <int NT, int S>
+__device__ __forceinline__ void dense_check_v(Smem (&sms)[S], const SegD& a, int c, NState& st,
+                                              float& vref, float& inv_vref) {
+  DRing& d = sms[a.grp].d;
+  const int b = c & 1, t = min(c * S + a.grp, a.n - 1), ov = d.ovf[b];
+  const bool mine = (ov >> 8) == t;
+  bool any = mine;
+  if (S == 2) {
+    const int o = S - 1 - a.grp;
+    any = mine || (sms[o].d.ovf[b] >> 8) == min(c * S + o, a.n - 1);
+  }
+  if (mine) {
+    const float nv = fmaxf(vref, __builtin_ldexpf(1.0f, max(-100, (ov & 0xff) - 134)));
+    const float f = vref / nv;
+#pragma unroll
+    for (int dg = 0; dg < 4; ++dg)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st.acc[dg][r] *= f;
+    vref = nv;
+    inv_vref = 1.0f / nv;
+    DenseRegs<NT> again;
+    dense_load_v<NT>(again, a, t);
+#pragma unroll
+    for (int i = 0; i < DenseRegs<NT>::kV; ++i)
+      fp_store_vpair(d.vb[b].v, again.v[2 * i], again.v[2 * i + 1], vslot(fp_vkey<NT>(i, 0)),
+                     fp_vchunk<NT>(i), inv_vref);
+  }
+  if (any) __syncthreads();
+}
+
+template <int NT, int S, int PH>
+__device__ __forceinline__ void segD_tile(Smem (&sms)[S], const SegD& a, int c, const v8bf (&qb)[8],
+                                          NState& st, const v8h (&pprev)[4], v8h (&pcur)[4],
+                                          DenseRegs<NT>& dr, float& vref, float& inv_vref) {
+  DRing& d = sms[a.grp].d;
+  auto tile = [&](int i) { return min(i * S + a.grp, a.n - 1); };
+  const bool dead = S > 1 && c * S + a.grp >= a.n;
+  const uint8_t* kb = d.k[PH];
+  v16f s[2];
+#pragma unroll
+  for (int kh = 0; kh < 2; ++kh) {
+    s[kh] = v16f{};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const v8bf ka = *reinterpret_cast<const v8bf*>(kb + (kh * 32 + a.col) * kKPitchBf + ks * 32 +
+                                                     a.half * 16);
+      s[kh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[ks], s[kh], 0, 0, 0);
+    }
+  }
+  if (c > 0) dense_check_v<NT, S>(sms, a, c - 1, st, vref, inv_vref);
+  dense_store_k<NT>(d.k[PH ^ 1], dr);
+  dense_store_v<NT>(d.vb[PH], d.ovf[PH], dr, tile(c), inv_vref);
+  dense_load_k<NT>(dr, a, tile(c + 2));
+  dense_load_v<NT>(dr, a, tile(c + 1));
+  const VBuf& prv = d.vb[PH ^ 1];
+  const v2h one2 = {(_Float16)1.0f, (_Float16)1.0f};
+  __builtin_amdgcn_s_setprio(1);
+  float ps = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int dg = i & 3, ks = i >> 2;
+    const v8h va = *reinterpret_cast<const v8h*>(prv.v + (dg * 32 + a.col) * kVPitch + ks * 32 +
+                                                 a.half * 16);
+    st.acc[dg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va, pprev[ks], st.acc[dg], 0, 0, 0);
+    const int kh = i >> 3, r = (i & 7) * 2;
+    v2h pk;
+    pk[0] = (_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(s[kh][r], a.alpha_log2e, -st.m));
+    pk[1] = (_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(s[kh][r + 1], a.alpha_log2e, -st.m));
+    ps = __builtin_amdgcn_fdot2(pk, one2, ps, false);
+    pcur[kh * 2 + (r >> 3)][r & 7] = pk[0];
+    pcur[kh * 2 + (r >> 3)][(r & 7) + 1] = pk[1];
+  }
+  // keep the fast-path weights next to the MFMAs (see segA_tile)
+  asm volatile("" : "+v"(pcur[0]), "+v"(pcur[1]), "+v"(pcur[2]), "+v"(pcur[3]), "+v"(ps));
+  __builtin_amdgcn_s_setprio(0);
+  const int p0 = (c * S + a.grp) * kTile;   // position of the tile's first key
+  if (dead || p0 + kTile - 1 > a.t0 || __ballot(!(ps <= kFastMax)) != 0) {
+    const int last = dead ? -1 : a.t0 + a.col - p0;   // last key of the tile the row sees
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[kh][r] = key_of(kh, r, a.half) <= last ? s[kh][r] : -INFINITY;
+    fp_softmax(st, s, a.alpha_log2e, pcur);
+  } else {
+    st.l += ps;
+  }
+  __syncthreads();
+}
+
 // Which keys the rows [t_first, t_last] of a workgroup see, and the reference
 // sVref of their head's V scales.  A quantized key at position p is seen by
 // rows t >= p + shift: shift = 0 for the fixed window, W for the per-query
@@ -1090,7 +1256,58 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
   }
 
   // ---------------- segments B and C: full-precision keys ----------------
-  if (fp_count > 0) {
+  if constexpr (BITS == 16) {
+    SegD a;
+    a.k0 = reinterpret_cast<const uint8_t*>(Kh);
+    a.v0 = reinterpret_cast<const uint8_t*>(Vh);
+    a.n = (fp_count + kTile - 1) / kTile;
+    a.grp = grp;
+    a.L = L;
+    a.t0 = t0;
+    a.alpha_log2e = alpha_log2e;
+    a.half = half;
+    a.col = col;
+    DRing& d = sm.d;
+    const int tid = group_tid<NT>(), steps = (a.n + S - 1) / S;
+    auto tile = [&](int i) { return min(i * S + grp, a.n - 1); };
+    DenseRegs<NT> dr;
+    dense_load_k<NT>(dr, a, tile(0));
+    v8bf qb[8];
+    const uint16_t* qrow = Q + (bh * L + (row_ok ? tq : 0)) * kHeadDim;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qb[ks] = *reinterpret_cast<const v8bf*>(qrow + ks * 16 + half * 8);
+    dense_store_k<NT>(d.k[0], dr);
+    dense_load_k<NT>(dr, a, tile(1));
+    dense_load_v<NT>(dr, a, tile(0));
+    // the V buffer that tile 0 multiplies by zero weights is cleared (no stale NaNs)
+    for (int i = tid; i < kVBytes / 16; i += NT)
+      reinterpret_cast<v4u*>(d.vb[1].v)[i] = v4u{0u, 0u, 0u, 0u};
+    if (tid == 0) d.ovf[0] = d.ovf[1] = -1;
+    __syncthreads();
+    v8h pa[4], pb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pa[i][e] = pb[i][e] = (_Float16)0.0f;
+    int c = 0;
+    for (; c + 1 < steps; c += 2) {
+      segD_tile<NT, S, 0>(sms, a, c, qb, st, pa, pb, dr, vref, inv_vref);
+      segD_tile<NT, S, 1>(sms, a, c + 1, qb, st, pb, pa, dr, vref, inv_vref);
+    }
+    if (c < steps) segD_tile<NT, S, 0>(sms, a, c, qb, st, pa, pb, dr, vref, inv_vref);
+    dense_check_v<NT, S>(sms, a, steps - 1, st, vref, inv_vref);
+    const v8h (&plast)[4] = (steps & 1) ? pb : pa;
+    const VBuf& lb = d.vb[(steps - 1) & 1];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int dg = 0; dg < 4; ++dg) {
+        const v8h va = *reinterpret_cast<const v8h*>(lb.v + (dg * 32 + col) * kVPitch + ks * 32 +
+                                                     half * 16);
+        st.acc[dg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va, plast[ks], st.acc[dg], 0, 0, 0);
+      }
+    if (S > 1) __syncthreads();   // the merge reuses the LDS
+  } else if (fp_count > 0) {
     v8bf qb[8];
     {
       const uint16_t* qrow = Q + (bh * L + (row_ok ? tq : 0)) * kHeadDim;
