@@ -1142,7 +1142,8 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
   const int g = Hq / Hkv;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int grp = wv / NW, w = wv % NW;
+  // (written so that one group folds: its LDS base and tile steps are constants)
+  const int grp = S == 1 ? 0 : wv / NW, w = S == 1 ? wv : wv % NW;
   Smem& sm = sms[grp];
   const int half = lane >> 5, col = lane & 31;
 
