@@ -58,7 +58,7 @@ def src_digest(*names):
 
 
 def attn_src_digest():
-    return src_digest("attn_prefill.hip", "codes_dev.h", "hyq_internal.h")
+    return src_digest("attn_prefill.hip", "attn_shape.h", "codes_dev.h", "hyq_internal.h")
 
 
 def decode_src_digest():

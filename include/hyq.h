@@ -218,8 +218,9 @@ HYQ_API int hyq_attn_prefill(const hyq_shape* shape, const void* Q, const void* 
                      void* out, int32_t out_dtype, void* stream);
 
 /* hyq_prefill - Algorithm 2 as one call: hyq_select_vertical (with no
- * scores output), hyq_quantize and hyq_attn_prefill on `stream`, in that
- * order.  Arguments, layouts, ownership and sizes are those of the three
+ * scores output), hyq_quantize and hyq_attn_prefill on `stream`, with the
+ * results of that order (the selection and the quantization share
+ * launches).  Arguments, layouts, ownership and sizes are those of the three
  * calls (ws / ws_bytes: the selection workspace); the arguments of all
  * three are validated before the first launch, so an invalid argument
  * returns HYQ_EINVAL with nothing launched.  Allocates nothing and keeps no
