@@ -1418,19 +1418,20 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
     if (grp == 1) return;
     const float M = fmaxf(st.m, mg.m[tid]);
     const float f0 = __builtin_amdgcn_exp2f(st.m - M), f1 = __builtin_amdgcn_exp2f(mg.m[tid] - M);
-    const float c0 = f0 * vref, c1 = f1 * mg.vref[tid];
+    // the row sum first: each state is scaled by its weight's share of it and
+    // never by sVref alone, so O * l (which may leave float32) is not formed
+    // (sVref is a power of two: sVref * rl is sVref / l)
+    const float rl = 1.0f / xhalf_sum(__builtin_fmaf(mg.l[tid], f1, st.l * f0));
+    const float c0 = f0 * (vref * rl), c1 = f1 * (mg.vref[tid] * rl);
 #pragma unroll
     for (int dg = 0; dg < 4; ++dg)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         st.acc[dg][r] = __builtin_fmaf(mg.acc[w][dg * 16 + r][lane], c1, st.acc[dg][r] * c0);
-    st.l = __builtin_fmaf(mg.l[tid], f1, st.l * f0);
-    vref = 1.0f;
   }
 
   // ---------------- finalize: O = acc * sVref / l ----------------
-  const float ltot = xhalf_sum(st.l);
-  const float sc = vref / ltot;
+  const float sc = S == 2 ? 1.0f : vref / xhalf_sum(st.l);
   if (!row_ok) return;
   const size_t obase = (bh * L + tq) * kHeadDim;
 #pragma unroll
@@ -1852,13 +1853,19 @@ attn_prefill_split_kernel(const uint16_t* __restrict__ Q, const uint16_t* __rest
   float M = mg.m[0][row];
 #pragma unroll
   for (int v = 1; v < kSplitWaves; ++v) M = fmaxf(M, mg.m[v][row]);
-  float l = 0.0f, o[8];
+  // the row sum before the accumulators, as in the kernel above
+  float f[kSplitWaves], l = 0.0f, o[8];
+#pragma unroll
+  for (int v = 0; v < kSplitWaves; ++v) {
+    f[v] = __builtin_amdgcn_exp2f(mg.m[v][row] - M);
+    l = __builtin_fmaf(mg.l[v][row], f[v], l);
+  }
+  const float rl = 1.0f / l;
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] = 0.0f;
 #pragma unroll
   for (int v = 0; v < kSplitWaves; ++v) {
-    const float f = __builtin_amdgcn_exp2f(mg.m[v][row] - M), fv = f * mg.vref[v];
-    l = __builtin_fmaf(mg.l[v][row], f, l);
+    const float fv = f[v] * (mg.vref[v] * rl);
 #pragma unroll
     for (int e4 = 0; e4 < 2; ++e4) {
       const float4 a = *reinterpret_cast<const float4*>(&mg.acc[v][row * kAccPitch + d0 + e4 * 4]);
@@ -1869,10 +1876,9 @@ attn_prefill_split_kernel(const uint16_t* __restrict__ Q, const uint16_t* __rest
     }
   }
   if (t0 + row >= L) return;
-  const float sc = 1.0f / l;
   const size_t at = (bh * L + t0 + row) * kHeadDim + d0;
-  store_out4<OUT_BF16>(out, at, o[0] * sc, o[1] * sc, o[2] * sc, o[3] * sc);
-  store_out4<OUT_BF16>(out, at + 4, o[4] * sc, o[5] * sc, o[6] * sc, o[7] * sc);
+  store_out4<OUT_BF16>(out, at, o[0], o[1], o[2], o[3]);
+  store_out4<OUT_BF16>(out, at + 4, o[4], o[5], o[6], o[7]);
 }
 
 template <int BITS, int OB, int FMT>

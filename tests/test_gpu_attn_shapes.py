@@ -71,3 +71,34 @@ def test_v_beyond_f16(kind, fmt):
     keep = ~np.isin(np.arange(128), [7, 20])
     mx, mean = gc.attention_error(G[..., keep], O[..., keep])
     assert gc.scaled_error(G, O) <= gc.TOL_MAX and mx <= gc.TOL_MAX and mean <= gc.TOL_MEAN
+
+
+# V so large that the unnormalised row sum (weights of up to L nearly equal
+# keys times V) leaves float32 although the output does not: every shape
+# divides by the row sum before it scales by V's reference.  (FP8 V codes:
+# with the reference at its largest, 2^100, block scales up to 2^107 keep
+# 448 * 2^7 within f16, so V may reach 448 * 2^107 = 7e34; int8 codes, whose
+# conversion adds 1152 * 2^e, end at 127 * 2^105 = 5e33.)
+@pytest.mark.parametrize("B,Hq,Hkv,L,fmt,v", [
+    (1, 5, 1, 1111, "bf16", 1e36), (2, 14, 2, 703, "bf16", 1e36), (1, 32, 8, 2501, "bf16", 1e36),
+    (1, 1, 1, 16384, "fp8", 3e34), (1, 2, 1, 16384, "fp8", 3e34)])
+def test_row_sum_beyond_float32(B, Hq, Hkv, L, fmt, v):
+    bits, f = FORMATS[fmt]
+    W = 128
+    d = gen.generate(6, 600 + L, B=B, Hq=Hq, Hkv=Hkv, L=L, D=128, W=W, plant=0.0)
+    d["Q"] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(d["Q"]) * np.float32(2.0 ** -6))
+    d["V"] = gen.f32_to_bf16_bits(np.float32(v) * (1 + np.float32(0.1) *
+                                                   gen.bf16_bits_to_f32(d["V"])))
+    shape = hyq.Shape(B=B, Hq=Hq, Hkv=Hkv, L=L, window=W, budget_ppm=10000, bits_kv=bits,
+                      kv_format=f)
+    assert v * 0.9 * L > float(np.finfo(np.float32).max)
+    t = tuple(gc.to_dev(d[n]) for n in ("Q", "K", "V"))
+    out = hyq.prefill(shape, *t, hyq.alloc_buffers(shape, t[0].device)).cpu().numpy()
+    idx, _ = orc.select_vertical(d["Q"], d["K"], Hkv, W, 10000)
+    qz = orc.quantize(d["Q"], d["K"], d["V"], idx, W, bits, fmt=gc.fmt_name(shape))
+    heads = [(B - 1, Hq - 1)]
+    rows = gc.sample_rows(L, W, 40, 1)
+    O = orc.attention(d["Q"], d["K"], d["V"], W, bits, idx, qz, heads=heads, rows=rows)
+    G = np.stack([out[b, h][rows] for b, h in heads])
+    mx, mean = gc.attention_error(G.astype(np.float64) / v, O.astype(np.float64) / v)
+    assert mx <= gc.TOL_MAX and mean <= gc.TOL_MEAN, (mx, mean)
