@@ -894,7 +894,8 @@ __device__ __forceinline__ void segA_tile(Smem& sm, const SegA& a, int c, const 
 struct SegD {
   const uint8_t* k0;
   const uint8_t* v0;
-  int n, grp, L;
+  int n, grp;
+  int rows;           // keys that some row of the workgroup sees: [0, rows)
   int t0;             // first query row of the wave
   float alpha_log2e;
   int half, col;
@@ -904,16 +905,18 @@ struct DenseRegs {
   static constexpr int kK = kTile * 16 / NT, kV = (kTile / 2) * 16 / NT;
   v4u k[kK], v[2 * kV];
 };
-// 16-byte chunk of a row of tile t (rows past L read the last one: hidden).
-__device__ __forceinline__ v4u dense_chunk(const uint8_t* base, int t, int key, int chunk, int L) {
-  const uint32_t row = (uint32_t)min(t * kTile + key, L - 1);
+// 16-byte chunk of a row of tile t.  Past the workgroup's last row, that row
+// again: a row that none of the queries sees must not be read, for its V meets
+// a zero weight (0 * inf) and takes part in the choice of sVref.
+__device__ __forceinline__ v4u dense_chunk(const uint8_t* base, int t, int key, int chunk, int rows) {
+  const uint32_t row = (uint32_t)min(t * kTile + key, rows - 1);
   return *reinterpret_cast<const v4u*>(base + (size_t)(row * (uint32_t)(kHeadDim * 2) + chunk * 16));
 }
 template <int NT>
 __device__ __forceinline__ void dense_load_k(DenseRegs<NT>& r, const SegD& a, int t) {
 #pragma unroll
   for (int i = 0; i < DenseRegs<NT>::kK; ++i)
-    r.k[i] = dense_chunk(a.k0, t, fp_kkey<NT>(i), (group_tid<NT>() + i * NT) & 15, a.L);
+    r.k[i] = dense_chunk(a.k0, t, fp_kkey<NT>(i), (group_tid<NT>() + i * NT) & 15, a.rows);
 }
 template <int NT>
 __device__ __forceinline__ void dense_load_v(DenseRegs<NT>& r, const SegD& a, int t) {
@@ -921,7 +924,7 @@ __device__ __forceinline__ void dense_load_v(DenseRegs<NT>& r, const SegD& a, in
   for (int i = 0; i < DenseRegs<NT>::kV; ++i)
 #pragma unroll
     for (int x = 0; x < 2; ++x)
-      r.v[2 * i + x] = dense_chunk(a.v0, t, fp_vkey<NT>(i, x), fp_vchunk<NT>(i), a.L);
+      r.v[2 * i + x] = dense_chunk(a.v0, t, fp_vkey<NT>(i, x), fp_vchunk<NT>(i), a.rows);
 }
 template <int NT>
 __device__ __forceinline__ void dense_store_k(uint8_t* kb, const DenseRegs<NT>& r) {
@@ -1263,7 +1266,7 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
     a.v0 = reinterpret_cast<const uint8_t*>(Vh);
     a.n = (fp_count + kTile - 1) / kTile;
     a.grp = grp;
-    a.L = L;
+    a.rows = fp_count;
     a.t0 = t0;
     a.alpha_log2e = alpha_log2e;
     a.half = half;

@@ -102,3 +102,30 @@ def test_row_sum_beyond_float32(B, Hq, Hkv, L, fmt, v):
     G = np.stack([out[b, h][rows] for b, h in heads])
     mx, mean = gc.attention_error(G.astype(np.float64) / v, O.astype(np.float64) / v)
     assert mx <= gc.TOL_MAX and mean <= gc.TOL_MEAN, (mx, mean)
+
+
+# A future V row must not reach earlier rows, however large or undefined it
+# is.  With 8 heads to a KV head a workgroup's rows end inside a 64-key tile
+# (8 or 4 units are 32 rows, as is kSplit8's one), so the rows before p are
+# bit for bit what they are with any other V from p on.
+@pytest.mark.parametrize("v", [np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("B,Hq,Hkv,L,fmt", [(1, 8, 1, 500, "bf16"), (1, 24, 3, 600, "bf16"),
+                                            (2, 64, 8, 600, "bf16"), (1, 8, 1, 500, "int8"),
+                                            (1, 24, 3, 900, "int8"), (2, 32, 4, 600, "int8"),
+                                            (2, 64, 8, 600, "int8")])
+def test_future_v_is_not_seen(B, Hq, Hkv, L, fmt, v):
+    bits, f = FORMATS[fmt]
+    W = 200
+    d = gen.generate(7, 700 + L, B=B, Hq=Hq, Hkv=Hkv, L=L, D=128, W=W, plant=0.02)
+    shape = hyq.Shape(B=B, Hq=Hq, Hkv=Hkv, L=L, window=W, budget_ppm=20000, bits_kv=bits,
+                      kv_format=f)
+    p = (L - 60) // 64 * 64 + 32   # in the window, the second half of a tile
+    assert L - W <= p < L
+    Q, K, V = (gc.to_dev(d[n]) for n in ("Q", "K", "V"))
+    out = []
+    for x in (1.0, v):
+        V[:, :, p:] = x
+        b = hyq.alloc_buffers(shape, V.device)
+        out.append(hyq.prefill(shape, Q, K, V, b)[:, :, :p].cpu().numpy())
+    assert np.isfinite(out[0]).all()
+    np.testing.assert_array_equal(out[1].view(np.uint32), out[0].view(np.uint32))
