@@ -142,16 +142,18 @@ def _derive(shape: Shape):
     return c, {n: getattr(z, n) for n, _ in _Sizes._fields_}
 
 
-# Pure functions of the shape's values (a frozen dataclass), which programs
-# pass again on every call: the struct (only ever read) and the sizes.
+# Pure functions of the shape's values, which programs pass again on every
+# call: the struct (only ever read) and the sizes.
 _derived_by_value = functools.lru_cache(maxsize=256)(_derive)
+_PLAIN = {int}
 
 
 def _derived(shape: Shape):
-    try:
+    # only plain ints are keys: other integer-like values may hash by identity
+    # and change, or not hash at all
+    if type(shape) is Shape and set(map(type, vars(shape).values())) == _PLAIN:
         return _derived_by_value(shape)
-    except TypeError:      # a field of an unhashable integer-like type
-        return _derive(shape)
+    return _derive(shape)
 
 
 def hyq_sizes_for(shape: Shape) -> dict:

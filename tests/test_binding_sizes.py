@@ -20,3 +20,22 @@ def test_errors_are_raised_every_time():
     for _ in range(2):
         with pytest.raises(hyq.HyqError):
             hyq.hyq_sizes_for(bad)
+
+
+def test_mutable_fields_are_read_on_every_call():
+    import torch
+    t = torch.tensor(300)   # hashes by identity
+    s = hyq.Shape(B=1, Hq=4, Hkv=2, L=t, window=64, budget_ppm=20000)
+    assert hyq.hyq_sizes_for(s)["P"] == 236
+    t += 200
+    assert hyq.hyq_sizes_for(s)["P"] == 436
+
+    class Duck:             # anything with a c()
+        L = 300
+
+        def c(self):
+            return hyq.Shape(B=1, Hq=4, Hkv=2, L=self.L, window=64, budget_ppm=20000).c()
+    d = Duck()
+    assert hyq.hyq_sizes_for(d)["P"] == 236
+    d.L = 500
+    assert hyq.hyq_sizes_for(d)["P"] == 436
