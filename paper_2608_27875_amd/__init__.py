@@ -333,7 +333,7 @@ def hyq_prefill(shape: Shape, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, 
 def alloc_buffers(shape: Shape, device, out_dtype: int = 0) -> dict:
     """Every intermediate and output buffer of one prefill call (torch tensors)."""
     torch = _torch()
-    sc, z = _derived(shape)
+    z = hyq_sizes_for(shape)
 
     def u8(n):
         return torch.empty(max(n, 0), dtype=torch.uint8, device=device)

@@ -39,3 +39,12 @@ def test_mutable_fields_are_read_on_every_call():
     assert hyq.hyq_sizes_for(d)["P"] == 236
     d.L = 500
     assert hyq.hyq_sizes_for(d)["P"] == 436
+
+
+def test_sizes_in_the_buffers_are_the_callers():
+    s = hyq.Shape(B=1, Hq=4, Hkv=2, L=300, window=64, budget_ppm=20000)
+    b = hyq.alloc_buffers(s, "cpu")
+    b["sizes"].update(k=-1, select_ws_bytes=0)
+    z = hyq.hyq_sizes_for(s)
+    assert z["k"] == 5 and z["select_ws_bytes"] > 0
+    assert hyq.alloc_buffers(s, "cpu")["sizes"] == z
