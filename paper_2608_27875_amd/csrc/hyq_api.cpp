@@ -137,6 +137,11 @@ SelectWs select_ws(const hyq_shape& s, const hyq_sizes& z, void* ws, float* scor
   return r;
 }
 
+bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
 int64_t round_up64(int64_t x) { return (x + 63) / 64 * 64; }
 
 // Geometry of the decode cache of a prefill shape (Algorithm 4's buffers);
@@ -386,7 +391,12 @@ HYQ_API int hyq_prefill(const hyq_shape* shape, const void* Q, const void* K, co
   if ((rc = check_attn_args(shape, z, Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes,
                             v_scale, kq_pos, softmax_scale, out, out_dtype)))
     return rc;
-  if (z.k > 0 && shape->bits_kv != 16) {
+  // The workspace is scratch of the selection alone, so a caller may carve it
+  // from memory that a later stage writes; Q codes written beside the
+  // selection must not land in it.
+  const bool apart = !overlaps(ws, z.select_ws_bytes, q_codes, z.q_codes_bytes) &&
+                     !overlaps(ws, z.select_ws_bytes, q_scale, z.q_scale_bytes);
+  if (z.k > 0 && shape->bits_kv != 16 && apart) {
     // the selection's launches carry the Q blocks; then the K/V blocks
     const hyq_shape& s = *shape;
     const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K);

@@ -99,3 +99,29 @@ def test_topk_prefix_lengths(P):
     hyq.hyq_select_vertical(shape, gc.to_dev(d["Q"]), gc.to_dev(d["K"]), b["idx"], None, b["ws"])
     idx, _ = orc.select_vertical(d["Q"], d["K"], 1, W, 30000)
     np.testing.assert_array_equal(b["idx"].cpu().numpy(), idx)
+
+
+# the selection's workspace may lie in memory that the quantization or the
+# attention writes afterwards
+@pytest.mark.parametrize("over", ["q_codes", "q_scale", "k_codes", "out"])
+@pytest.mark.parametrize("sel", [0, 1])
+def test_prefill_with_the_workspace_in_a_later_buffer(over, sel):
+    import torch
+    d = gen.generate(1, 301, B=2, Hq=6, Hkv=2, L=1000, D=128, W=100, plant=0.02)
+    shape = hyq.Shape(B=2, Hq=6, Hkv=2, L=1000, window=100, budget_ppm=50000, bits_kv=8,
+                      selector=sel)
+    t = tuple(gc.to_dev(d[n]) for n in ("Q", "K", "V"))
+    g = gc.run_gpu(shape, d, tensors=t)
+    b = hyq.alloc_buffers(shape, t[0].device)
+    own = b[over].numel() * b[over].element_size()
+    n = max(own, b["ws"].numel())
+    mem = torch.zeros((n + 15) // 16 * 16, dtype=torch.uint8, device=t[0].device)
+    b["ws"] = mem[:b["ws"].numel()]
+    b[over] = mem[:own].view(b[over].dtype).view(b[over].shape)
+    out = hyq.prefill(shape, *t, b)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), g["out"].view(np.uint32))
+    np.testing.assert_array_equal(b["idx"].cpu().numpy(), g["idx"])
+    for n in BUFS:
+        np.testing.assert_array_equal(b[n].cpu().numpy().view(np.uint8), g[n].view(np.uint8),
+                                      err_msg=n)
