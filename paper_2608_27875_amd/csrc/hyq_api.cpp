@@ -396,13 +396,13 @@ HYQ_API int hyq_prefill(const hyq_shape* shape, const void* Q, const void* K, co
   // selection must not land in it.
   const bool apart = !overlaps(ws, z.select_ws_bytes, q_codes, z.q_codes_bytes) &&
                      !overlaps(ws, z.select_ws_bytes, q_scale, z.q_scale_bytes);
-  if (z.k > 0 && shape->bits_kv != 16 && apart) {
+  const hyq_shape& s = *shape;
+  const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K);
+  const hyq::QuantQ qq = hyq::quant_q_all(s, z, q, q_codes, q_scale);
+  if (z.k > 0 && s.bits_kv != 16 && apart && hyq::prefill_fuses(s, qq)) {
     // the selection's launches carry the Q blocks; then the K/V blocks
-    const hyq_shape& s = *shape;
-    const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const SelectWs w = select_ws(s, z, ws, nullptr);
-    const hyq::QuantQ qq = hyq::quant_q_all(s, z, q, q_codes, q_scale);
     const hipError_t e = hyq::launch_select(s, z, q, k, idx, w.scores, w.qsum, w.hist, w.tws, w.cm,
                                             &qq, st);
     if (e != hipSuccess) return hip_status(e, "hyq_prefill selection launch");

@@ -32,9 +32,11 @@ void launch_quant_q(const QuantQ& q, hipStream_t st);
 // ([B][Hkv][P], may be the caller's output), qsum (the per-head tail sums,
 // [B][Hq][D]), hist ([B][Hkv][kSelHistBins] key counts), tws
 // (select_topk_ws_bytes of top-k candidates and bitmaps), cm_ws (the column
-// mass's scratch).  With qq also those Q blocks, beside the selection's own
-// work.  A no-op when k = 0.
+// mass's scratch).  With qq (only where prefill_fuses: both then fit one grid
+// dimension) also those Q blocks, beside the selection's own work.  A no-op
+// when k = 0.
 size_t select_topk_ws_bytes(int BH, int P);
+bool prefill_fuses(const hyq_shape& s, const QuantQ& qq);
 hipError_t launch_select(const hyq_shape& s, const hyq_sizes& z, const uint16_t* Q,
                          const uint16_t* K, int32_t* idx, float* scores, float* qsum,
                          uint32_t* hist, uint32_t* tws, float* cm_ws, const QuantQ* qq,

@@ -94,7 +94,7 @@ template <int FMT>
 __global__ void __launch_bounds__(kQuantThreads)
 quant_q_kernel(QuantQ q) {
   __shared__ float red[kQuantThreads / 64];
-  quant_q_block<FMT>(q, (int)blockIdx.x, red);
+  quant_q_block<FMT>(q, (int)(blockIdx.y * gridDim.x + blockIdx.x), red);
 }
 
 // The codes of a thread's 32 values of a block with scale s.
@@ -306,7 +306,7 @@ QuantQ quant_q_all(const hyq_shape& s, const hyq_sizes& z, const uint16_t* Q, in
 
 void launch_quant_q(const QuantQ& q, hipStream_t st) {
   if (q.count <= 0) return;
-  const int grid = q.count;
+  const dim3 grid(q.n_qblk, q.count / q.n_qblk);
   if (q.fmt == HYQ_FMT_FP4Q6) quant_q_kernel<HYQ_FMT_FP4Q6><<<grid, kQuantThreads, 0, st>>>(q);
   else if (q.fmt == HYQ_FMT_FP8) quant_q_kernel<HYQ_FMT_FP8><<<grid, kQuantThreads, 0, st>>>(q);
   else quant_q_kernel<HYQ_FMT_INT><<<grid, kQuantThreads, 0, st>>>(q);

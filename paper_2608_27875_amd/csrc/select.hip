@@ -76,6 +76,7 @@ __device__ __forceinline__ TopkWs topk_ws(uint32_t* base, int bj, int P) {
 constexpr int kTailRows = 256;
 constexpr int kTailThreads = kTailRows;
 constexpr int kTailCh = 16;   // channels per workgroup
+constexpr int kTailGroups = kHeadDim / kTailCh;
 // Workgroups from n_tail on quantize one Q block each instead.
 template <int QFMT>
 __global__ void __launch_bounds__(kTailThreads)
@@ -83,11 +84,12 @@ tail_proxy_kernel(const uint16_t* __restrict__ Q, float* __restrict__ qpart,
                   uint32_t* __restrict__ hist, uint32_t* __restrict__ tws, int BHq, int g, int L,
                   int t, int P, int n_tail, QuantQ qq) {
   __shared__ uint4 rows[kTailRows][kTailCh / 8];
-  if ((int)blockIdx.x >= n_tail) {
-    quant_q_block<QFMT>(qq, (int)blockIdx.x - n_tail, reinterpret_cast<float*>(&rows[0][0]));
+  const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  if (wg >= n_tail) {
+    quant_q_block<QFMT>(qq, wg - n_tail, reinterpret_cast<float*>(&rows[0][0]));
     return;
   }
-  const int bh = (int)blockIdx.x % BHq, cg = (int)blockIdx.x / BHq, c0 = cg * kTailCh;
+  const int bh = wg % BHq, cg = wg / BHq, c0 = cg * kTailCh;
   if (bh % g == 0 && cg == 0) {
     uint32_t* hj = hist + (size_t)(bh / g) * kSelHistBins;
     for (int i = threadIdx.x; i < kSelHistBins; i += kTailThreads) hj[i] = 0u;
@@ -575,6 +577,10 @@ topk_final_kernel(uint32_t* __restrict__ tws, int32_t* __restrict__ idx, int P, 
 
 }  // namespace
 
+bool prefill_fuses(const hyq_shape& s, const QuantQ& qq) {
+  return ((int64_t)s.B * s.Hq * kTailGroups + qq.count) * kTailThreads < (int64_t)1 << 32;
+}
+
 size_t select_topk_ws_bytes(int BH, int P) { return (size_t)BH * topk_ws_words(P) * 4; }
 
 namespace {
@@ -582,10 +588,13 @@ namespace {
 template <int QFMT>
 void launch_tail_proxy(const hyq_shape& s, const uint16_t* Q, float* qsum, uint32_t* hist,
                        uint32_t* tws, int t, int P, const QuantQ& qq, hipStream_t st) {
-  const int BHq = s.B * s.Hq, n_tail = BHq * (kHeadDim / kTailCh);
+  const int BHq = s.B * s.Hq, n_tail = BHq * kTailGroups;
   static_assert(kTailThreads == kQuantThreads, "both kinds of workgroup share the launch");
-  tail_proxy_kernel<QFMT><<<n_tail + qq.count, kTailThreads, 0, st>>>(
-      Q, qsum, hist, tws, BHq, s.Hq / s.Hkv, s.L, t, P, n_tail, qq);
+  // a dimension of a launch holds fewer than 2^32 threads (prefill_fuses keeps
+  // the two kinds together below that)
+  const dim3 grid = qq.count ? dim3(n_tail + qq.count) : dim3(BHq, kTailGroups);
+  tail_proxy_kernel<QFMT><<<grid, kTailThreads, 0, st>>>(Q, qsum, hist, tws, BHq, s.Hq / s.Hkv, s.L,
+                                                         t, P, n_tail, qq);
 }
 
 template <int QFMT>

@@ -125,3 +125,24 @@ def test_prefill_with_the_workspace_in_a_later_buffer(over, sel):
     for n in BUFS:
         np.testing.assert_array_equal(b[n].cpu().numpy().view(np.uint8), g[n].view(np.uint8),
                                       err_msg=n)
+
+
+# 2^21 query heads: eight tail-proxy workgroups each are 2^32 threads, more
+# than one dimension of a launch holds
+def test_select_over_very_many_heads():
+    import torch
+    B, g = 1 << 18, 8
+    shape = hyq.Shape(B=B, Hq=g, Hkv=1, L=2, window=1, budget_ppm=1000000)
+    gen_ = torch.Generator(device="cuda").manual_seed(8)
+    Q = torch.randn((B, g, 2, 128), generator=gen_, device="cuda", dtype=torch.bfloat16)
+    K = torch.randn((B, 1, 2, 128), generator=gen_, device="cuda", dtype=torch.bfloat16)
+    z = hyq.hyq_sizes_for(shape)
+    idx = torch.full((B, 1, z["k"]), -1, dtype=torch.int32, device="cuda")
+    scores = torch.full((B, 1, z["P"]), float("nan"), device="cuda")
+    ws = torch.empty(z["select_ws_bytes"], dtype=torch.uint8, device="cuda")
+    hyq.hyq_select_vertical(shape, Q, K, idx, scores, ws)
+    assert int(idx.abs().max()) == 0
+    want = (Q[:, :, 1].double().sum(1) * K[:, 0, 0].double()).sum(-1)
+    # 7 float32 additions per channel, 128 products, a tree of 7 levels
+    bound = 15 * 2.0 ** -24 * (Q[:, :, 1].double().abs().sum(1) * K[:, 0, 0].double().abs()).sum(-1)
+    assert bool(((scores[:, 0, 0].double() - want).abs() <= bound).all())
