@@ -24,9 +24,9 @@
 //     bits of the threshold; the chosen positions are written in ascending
 //     order (ordered compaction of the bitmaps; keys equal to the threshold
 //     lowest position first).
-// Up to kWholeKeys keys per head, one workgroup per head does all of that in
-// one launch (topk_kernel); longer prefixes classify on many workgroups first
-// (topk_classify_kernel, topk_final_kernel).
+// On short prefixes, and on longer ones of many heads (one_launch), one
+// workgroup per head does all of that in one launch (topk_kernel); the others
+// classify on many workgroups first (topk_classify_kernel, topk_final_kernel).
 //
 // A prefill's Q quantization needs nothing of the selection: its blocks ride
 // along as extra workgroups of the tail-proxy launch, which alone is bound by
@@ -428,12 +428,12 @@ constexpr int kWholeKeys = kMapWords * 32;     // longest prefix of topk_kernel
 constexpr int kKeyBatch = 8;                   // keys per thread loaded together
 
 // The whole top-k of one (b, j) per workgroup.  One workgroup reads a head's
-// scores at about one CU's L2 rate, which costs less than a second launch and
-// the round trip of bitmap and candidates through memory (32k, 8
-// heads: classification 4.8 us, final 8.3 us and the gap between them before,
-// 12.4 us now; 1k, one head: 3.0 + 3.9 us, now 4.7 us).  Short
-// prefixes are bound by the chain of barriers, so the block scans use DPP
-// within the waves and one barrier each.
+// scores at about one CU's L2 rate (a microsecond per 4096 keys), which on
+// short prefixes, or with enough heads to occupy the chip, costs less than a
+// second launch and the round trip of bitmap and candidates through memory
+// (one_launch; 1k, one head: classification 3.0 us + final 3.9 us, here 4.7).
+// Short prefixes are bound by the chain of barriers, so the block scans use
+// DPP within the waves and one barrier each.
 __global__ void __launch_bounds__(kTopkThreads)
 topk_kernel(const float* __restrict__ S, const uint32_t* __restrict__ hist,
             uint32_t* __restrict__ tws, int32_t* __restrict__ idx, int P, int k) {
@@ -516,7 +516,7 @@ topk_kernel(const float* __restrict__ S, const uint32_t* __restrict__ hist,
   }
 }
 
-// Final top-k of a prefix longer than kWholeKeys, one workgroup per (b, j):
+// Final top-k after the classification, one workgroup per (b, j):
 //  1. the bin of the k-th largest key (from the classification) and the
 //     candidates, of which each wave takes a contiguous share (its first
 //     kLdsCap into LDS);
@@ -577,6 +577,22 @@ topk_final_kernel(uint32_t* __restrict__ tws, int32_t* __restrict__ idx, int P, 
 
 }  // namespace
 
+// Whether topk_kernel takes a prefix of P keys of each of `heads` KV heads.
+// The whole selection in microseconds, one launch / classification and final:
+//   heads    16k            24k            32k            48k            64k            128k
+//     1   17.6 /  17.6   20.0 /  19.9   22.0 /  20.1   27.2 /  23.0   31.8 /  26.3   48.8 /  33.4
+//     8   19.0 /  19.8   25.8 /  25.9   29.6 /  29.5   39.4 /  36.9   47.4 /  43.9   84.8 /  75.6
+//    16   28.0 /  28.9   34.8 /  34.9   41.8 /  41.5   55.1 /  54.0   70.1 /  67.8    143 /   136
+//    24                  41.0 /  42.2   50.3 /  50.9   70.0 /  70.0    103 /  99.4    194 /   193
+//    32   38.9 /  40.9   47.4 /  48.7   60.8 /  61.7    101 /   101    125 /   124    253 /   250
+//    64   57.3 /  61.7   95.3 /  98.2    118 /   121    174 /   179    231 /   235    465 /   472
+//   128    116 /   125    168 /   177    220 /   231    323 /   340    425 /   445
+// The lines cross at about 24k keys up to 16 heads, then at 1536 per head; from
+// 48 heads on (98k: 259.5 / 259.2, 128k: 353.3 / 353.3) they do not cross.
+static bool one_launch(int heads, int P) {
+  return P <= kWholeKeys && (P <= 24576 || heads >= 48 || P <= heads * 1536);
+}
+
 bool prefill_fuses(const hyq_shape& s, const QuantQ& qq) {
   return ((int64_t)s.B * s.Hq * kTailGroups + qq.count) * kTailThreads < (int64_t)1 << 32;
 }
@@ -618,7 +634,7 @@ hipError_t launch_select_t(const hyq_shape& s, const hyq_sizes& z, const uint16_
     score_kernel<<<dim3(BH, (z.P + kScoreRows - 1) / kScoreRows), kScoreThreads, 0, st>>>(
         K, qsum, scores, hist, g, s.L, z.P);
   }
-  if (z.P <= kWholeKeys) {
+  if (one_launch(BH, z.P)) {
     topk_kernel<<<BH, kTopkThreads, 0, st>>>(scores, hist, tws, idx, z.P, z.k);
   } else {
     const dim3 cg(BH, (z.P + kTopkThreads - 1) / kTopkThreads);

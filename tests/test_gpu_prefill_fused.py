@@ -1,6 +1,6 @@
 """hyq_prefill shares launches between selection and quantization, the top-k
-runs as one launch up to 131072 prefix keys, and the K/V quantizer finds its
-rows from the vertical list: each against the oracle or the three calls at
+runs as one launch on short prefixes and on longer ones of many heads, and the
+K/V quantizer finds its rows from the vertical list: each against the oracle or the three calls at
 the sizes where it can go wrong."""
 import numpy as np
 import pytest
@@ -88,7 +88,7 @@ def test_partition_of_clustered_lists(kind):
     assert np.all(got[len(want):] == hyq.KQ_POS_PAD)
 
 
-# both sides of the longest prefix of the one-launch top-k, and its shortest
+# the shortest prefixes, and both sides of a window of the final pass's bitmaps
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("P", [1, 63, 1024, 1025, 8192, 131072, 131073])
 def test_topk_prefix_lengths(P):
@@ -125,6 +125,27 @@ def test_prefill_with_the_workspace_in_a_later_buffer(over, sel):
     for n in BUFS:
         np.testing.assert_array_equal(b[n].cpu().numpy().view(np.uint8), g[n].view(np.uint8),
                                       err_msg=n)
+
+
+# both sides of the lines between the one-launch top-k and the classification:
+# 24576 keys, then 1536 per head, from 48 heads on 131072.  The scores are
+# checked elsewhere, here the choice among them.
+@pytest.mark.parametrize("heads,P", [(1, 24576), (1, 24577), (17, 26112), (17, 26113), (48, 131072),
+                                     (48, 131073)])
+def test_topk_lines(heads, P):
+    import torch
+    W = 64
+    shape = hyq.Shape(B=1, Hq=heads, Hkv=heads, L=P + W, window=W, budget_ppm=20000)
+    gen_ = torch.Generator(device="cuda").manual_seed(9)
+    Q, K = (torch.randn((1, heads, P + W, 128), generator=gen_, device="cuda",
+                        dtype=torch.bfloat16) for _ in range(2))
+    z = hyq.hyq_sizes_for(shape)
+    idx = torch.empty((1, heads, z["k"]), dtype=torch.int32, device="cuda")
+    scores = torch.empty((1, heads, P), device="cuda")
+    ws = torch.empty(z["select_ws_bytes"], dtype=torch.uint8, device="cuda")
+    hyq.hyq_select_vertical(shape, Q, K, idx, scores, ws)
+    order = torch.sort(scores, dim=-1, descending=True, stable=True).indices[..., :z["k"]]
+    assert torch.equal(idx.long(), order.sort().values)
 
 
 # 2^21 query heads: eight tail-proxy workgroups each are 2^32 threads, more
