@@ -957,7 +957,7 @@ __device__ __forceinline__ void dense_check_v(Smem (&sms)[S], const SegD& a, int
   DRing& d = sms[a.grp].d;
   const int b = c & 1, t = min(c * S + a.grp, a.n - 1), ov = d.ovf[b];
   const bool mine = (ov >> 8) == t;
-  bool any = mine;
+  bool any = false;   // S = 2: either group's tile
   if (S == 2) {
     const int o = S - 1 - a.grp;
     any = mine || (sms[o].d.ovf[b] >> 8) == min(c * S + o, a.n - 1);
@@ -977,6 +977,7 @@ __device__ __forceinline__ void dense_check_v(Smem (&sms)[S], const SegD& a, int
     for (int i = 0; i < DenseRegs<NT>::kV; ++i)
       fp_store_vpair(d.vb[b].v, again.v[2 * i], again.v[2 * i + 1], vslot(fp_vkey<NT>(i, 0)),
                      fp_vchunk<NT>(i), inv_vref);
+    if (S == 1) __syncthreads();
   }
   if (any) __syncthreads();
 }
@@ -1348,8 +1349,8 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
         // is for both groups, whichever has such a tile.
         const int ov = cur.ovf;
         const bool mine = (ov >> 8) == ft;
-        const bool any = S == 1 ? mine
-                                : mine || (sms[S - 1 - grp].f[f & 1].ovf >> 8) == f * S + (S - 1 - grp);
+        const bool any = S > 1 &&
+                         (mine || (sms[S - 1 - grp].f[f & 1].ovf >> 8) == f * S + (S - 1 - grp));
         if (mine) {
           const int ex = max(-100, (ov & 0xff) - 134);
           const float nv = fmaxf(vref, __builtin_ldexpf(1.0f, ex));
@@ -1361,6 +1362,7 @@ attn_prefill_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
           vref = nv;
           inv_vref = 1.0f / nv;
           fp_restage_v<NT>(cur, Vh, L, inv_vref);
+          if (S == 1) __syncthreads();
         }
         if (any) __syncthreads();
       }
