@@ -1898,8 +1898,9 @@ hipError_t launch_t(const hyq_shape& s, const hyq_sizes& z, const uint16_t* Q,
 #define HYQ_ARGS                                                                              \
   Q, K, V, idx, q_codes, q_scale, k_codes, k_scale, v_codes, v_scale, kq_pos, out, s.Hq, s.Hkv, \
       nbj, s.L, z.P, z.k, z.nQ, z.n_qblk, z.n_kvblk, softmax_scale * kLog2e, band_w
-  const AttnShape sh = choose_attn_shape(units, nbj, (s.L + kTile - 1) / kTile, BITS == 16,
-                                         device_cus());
+  const AttnKeys keys = attn_keys((int64_t)z.k + (s.window < s.L ? s.window : s.L), s.L, BITS == 16,
+                                  band_w > 0);
+  const AttnShape sh = choose_attn_shape(units, nbj, (s.L + kTile - 1) / kTile, keys, device_cus());
   const int n = (int)(sh.grid / nbj);   // workgroups per KV head
   const dim3 grid((unsigned)sh.grid);
   switch (sh.kind) {

@@ -13,16 +13,22 @@ from paper_2608_27875_amd import gen
 hyq = gc.hyq
 pytestmark = pytest.mark.gpu
 
-# kind: (B, Hq, Hkv, L); 32-row units in all -> split8: 5, 175; split2: 616;
-# half: 1520; full: 2528
-SHAPES = {"split8_tiny": (1, 1, 1, 131), "split8": (1, 5, 1, 1111), "split2": (2, 14, 2, 703),
+# kind: (B, Hq, Hkv, L), and where nothing quantized takes another kind (a test of
+# the policy checks each).  32-row units in all -> split8: 5, 175 (110);
+# split2: 924; half: 1520 (520); full: 2528
+SHAPES = {"split8_tiny": (1, 1, 1, 131), "split8": (1, 5, 1, 1111), "split2": (2, 14, 2, 1051),
           "half": (1, 40, 8, 1201), "full": (1, 32, 8, 2501)}
+DENSE_SHAPES = {"split8": (1, 5, 1, 700), "half": (1, 40, 8, 401)}
 FORMATS = {"int8": (8, hyq.FMT_INT), "int4": (4, hyq.FMT_INT), "fp8": (8, hyq.FMT_FP8),
            "fp4": (4, hyq.FMT_FP4), "fp4q6": (4, hyq.FMT_FP4Q6), "bf16": (16, hyq.FMT_INT)}
 
 
+def shape_for(kind, fmt):
+    return DENSE_SHAPES.get(kind, SHAPES[kind]) if fmt == "bf16" else SHAPES[kind]
+
+
 def _run(kind, fmt, W, band=False, big_v=()):
-    B, Hq, Hkv, L = SHAPES[kind]
+    B, Hq, Hkv, L = shape_for(kind, fmt)
     bits, f = FORMATS[fmt]
     d = gen.generate(5, 500 + L, B=B, Hq=Hq, Hkv=Hkv, L=L, D=128, W=W, plant=0.03)
     if big_v:
@@ -66,7 +72,7 @@ def test_band(kind, fmt):
 @pytest.mark.parametrize("fmt", ["int8", "bf16"])
 @pytest.mark.parametrize("kind", ["split8", "split2", "half", "full"])
 def test_v_beyond_f16(kind, fmt):
-    L = SHAPES[kind][3]
+    L = shape_for(kind, fmt)[3]
     G, O = _run(kind, fmt, W=200, big_v=[(L - 170, 7, 1.0e5), (L - 60, 20, -3.0e6)])
     keep = ~np.isin(np.arange(128), [7, 20])
     mx, mean = gc.attention_error(G[..., keep], O[..., keep])
@@ -79,12 +85,16 @@ def test_v_beyond_f16(kind, fmt):
 # with the reference at its largest, 2^100, block scales up to 2^107 keep
 # 448 * 2^7 within f16, so V may reach 448 * 2^107 = 7e34; int8 codes, whose
 # conversion adds 1152 * 2^e, end at 127 * 2^105 = 5e33.)
-@pytest.mark.parametrize("B,Hq,Hkv,L,fmt,v", [
-    (1, 5, 1, 1111, "bf16", 1e36), (2, 14, 2, 703, "bf16", 1e36), (1, 32, 8, 2501, "bf16", 1e36),
-    (1, 1, 1, 16384, "fp8", 3e34), (1, 2, 1, 16384, "fp8", 3e34)])
-def test_row_sum_beyond_float32(B, Hq, Hkv, L, fmt, v):
+ROW_SUM = [("split8", 1, 5, 1, 700, "bf16", 1e36), ("split2", 2, 14, 2, 703, "bf16", 1e36),
+           ("full", 1, 32, 8, 2501, "bf16", 1e36), ("split8", 1, 1, 1, 16384, "fp8", 3e34),
+           ("split2", 1, 2, 1, 16384, "fp8", 3e34)]
+ROW_SUM_W = 128
+
+
+@pytest.mark.parametrize("kind,B,Hq,Hkv,L,fmt,v", ROW_SUM)
+def test_row_sum_beyond_float32(kind, B, Hq, Hkv, L, fmt, v):
     bits, f = FORMATS[fmt]
-    W = 128
+    W = ROW_SUM_W
     d = gen.generate(6, 600 + L, B=B, Hq=Hq, Hkv=Hkv, L=L, D=128, W=W, plant=0.0)
     d["Q"] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(d["Q"]) * np.float32(2.0 ** -6))
     d["V"] = gen.f32_to_bf16_bits(np.float32(v) * (1 + np.float32(0.1) *
@@ -108,14 +118,18 @@ def test_row_sum_beyond_float32(B, Hq, Hkv, L, fmt, v):
 # is.  With 8 heads to a KV head a workgroup's rows end inside a 64-key tile
 # (8 or 4 units are 32 rows, as is kSplit8's one), so the rows before p are
 # bit for bit what they are with any other V from p on.
+FUTURE_V = [("split8", 1, 8, 1, 500, "bf16"), ("split2", 1, 24, 3, 600, "bf16"),
+            ("half", 1, 24, 3, 400, "bf16"), ("full", 2, 64, 8, 600, "bf16"),
+            ("split8", 1, 8, 1, 500, "int8"), ("split2", 1, 24, 3, 1100, "int8"),
+            ("half", 2, 32, 4, 600, "int8"), ("full", 2, 64, 8, 600, "int8")]
+FUTURE_V_W = 200
+
+
 @pytest.mark.parametrize("v", [np.inf, np.nan, 3e38])
-@pytest.mark.parametrize("B,Hq,Hkv,L,fmt", [(1, 8, 1, 500, "bf16"), (1, 24, 3, 600, "bf16"),
-                                            (2, 64, 8, 600, "bf16"), (1, 8, 1, 500, "int8"),
-                                            (1, 24, 3, 900, "int8"), (2, 32, 4, 600, "int8"),
-                                            (2, 64, 8, 600, "int8")])
-def test_future_v_is_not_seen(B, Hq, Hkv, L, fmt, v):
+@pytest.mark.parametrize("kind,B,Hq,Hkv,L,fmt", FUTURE_V)
+def test_future_v_is_not_seen(kind, B, Hq, Hkv, L, fmt, v):
     bits, f = FORMATS[fmt]
-    W = 200
+    W = FUTURE_V_W
     d = gen.generate(7, 700 + L, B=B, Hq=Hq, Hkv=Hkv, L=L, D=128, W=W, plant=0.02)
     shape = hyq.Shape(B=B, Hq=Hq, Hkv=Hkv, L=L, window=W, budget_ppm=20000, bits_kv=bits,
                       kv_format=f)
