@@ -151,22 +151,9 @@ __device__ __forceinline__ float xhalf_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Number of entries <= x in the ascending array a[0, n) (wave-cooperative
-// 64-ary search; every lane returns the same value).
+// Number of entries <= x in the ascending array a[0, n).
 __device__ int count_le(const int32_t* __restrict__ a, int n, int x) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, hi = n;  // answer in [lo, hi]
-  while (hi > lo) {
-    const int step = (hi - lo + 63) / 64;
-    const int i = lo + (lane + 1) * step - 1;
-    const bool pred = i < hi && a[i] <= x;
-    const int cnt = __popcll(__ballot(pred));
-    lo = lo + cnt * step;
-    const int nhi = lo + step - 1;
-    hi = nhi < hi ? nhi : hi;
-    if (step == 1) break;
-  }
-  return lo;
+  return wave_search(n, [=](int i) { return a[i] <= x; });
 }
 
 // Slot of key e (0..63) in the permuted V^T row.

@@ -106,6 +106,22 @@ constexpr int kBlock = 64;
 // Top-k key histogram: bins of the top kSelHistBits bits of the score order key.
 constexpr int kSelHistBits = 12;
 constexpr int kSelHistBins = 1 << kSelHistBits;
+// Number of i in [0, n) for which holds(i), a predicate that turns false once
+// (wave-cooperative 64-ary search; every lane returns the same value).
+template <class Pred>
+__device__ __forceinline__ int wave_search(int n, Pred holds) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = n;   // answer in [lo, hi]
+  while (hi > lo) {
+    const int step = (hi - lo + 63) / 64;
+    const int i = lo + (lane + 1) * step - 1;
+    const bool pred = i < hi && holds(i);
+    lo += (int)__popcll(__ballot(pred)) * step;
+    hi = min(hi, lo + step - 1);
+    if (step == 1) break;
+  }
+  return lo;
+}
 // Order-preserving map float -> uint32 (larger float, larger key); -0 -> +0.
 __device__ __forceinline__ uint32_t order_key(float f) {
   uint32_t u = __float_as_uint(f + 0.0f);   // -0 + 0 = +0

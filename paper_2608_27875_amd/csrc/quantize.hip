@@ -28,20 +28,9 @@ namespace {
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 // Number of the ascending a[0, n) with a[i] - i <= x: the vertical positions
-// that precede the x-th (from 0) non-vertical one.  Wave-cooperative 64-ary
-// search; every lane returns the same value.
+// that precede the x-th (from 0) non-vertical one.
 __device__ __forceinline__ int verticals_before(const int32_t* __restrict__ a, int n, int x) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, hi = n;   // answer in [lo, hi]
-  while (hi > lo) {
-    const int step = (hi - lo + 63) / 64;
-    const int i = lo + (lane + 1) * step - 1;
-    const bool pred = i < hi && a[i] - i <= x;
-    lo += (int)__popcll(__ballot(pred)) * step;
-    hi = min(hi, lo + step - 1);
-    if (step == 1) break;
-  }
-  return lo;
+  return wave_search(n, [=](int i) { return a[i] - i <= x; });
 }
 
 // Positions of the 64 slots [n0, n0 + 64) of a head (the n-th non-vertical
