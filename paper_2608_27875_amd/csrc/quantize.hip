@@ -15,8 +15,8 @@
 // Every quotient is the IEEE correctly rounded float32 quotient (for bf16
 // inputs by the block's reciprocal and a residual correction, see
 // recip_quotient) and rint rounds half to even, so codes match the definition
-// bit for bit.  HBM-bound: each input row is read once and each
-// code written once, with 16-byte accesses.
+// bit for bit.  HBM-bound: each input row is read once, 16 bytes a load, and
+// each code written once (Q 8 bytes a store, K and V 16).
 #include "hyq_internal.h"
 #include "quant_dev.h"
 

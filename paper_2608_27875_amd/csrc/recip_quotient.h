@@ -11,7 +11,8 @@
 namespace hyq {
 
 // With r = fl32(1 / s): q = x * r, then one residual correction
-// q + r * (x - q * s).  For bf16 x with |x| <= amax and s = fl32(amax / c),
+// q + r * (x - q * s) with fused multiply-adds (the last step of Markstein's
+// division, IBM Journal of Research and Development 34, 1990).  For bf16 x with |x| <= amax and s = fl32(amax / c),
 // c one of 127, 7, 448, 6, 7.5, this is the correctly rounded float32
 // quotient x / s, apart from the sign of a zero: tests/recip_check.cpp goes
 // through every pair of mantissas and every exponent difference that can give
