@@ -94,9 +94,9 @@ __device__ __forceinline__ int quant_code(float x, float s, float c) {
 // recip_ok(s): three operations (and the sign of x, which the floating-point
 // codes keep for -0) instead of about twelve, which held the quantization
 // kernels back as much as memory did (Q at 32k, 32 heads, 402 MB: 76.1 us
-// before, 64.7 us with the tail proxy in the same launch; K and V at 32k, 8
-// heads, int4: 42.5 us before, 36.7 us with the partition and Freeze's gather
-// in the same launch).
+// before, 62.9 us now, each in a launch of its own; K and V at 32k, 8 heads,
+// int4: 42.5 us before, 36.7 us although the partition and Freeze's gather
+// joined the launch).
 template <int FMT>
 __device__ __forceinline__ float quot(float x, float s, float r) {
   const float y = recip_quotient(x, s, r);

@@ -30,7 +30,7 @@
 //
 // A prefill's Q quantization needs nothing of the selection: its blocks ride
 // along as extra workgroups of the tail-proxy launch, which alone is bound by
-// latency (32k: 7.7 us, and 76 us for Q in a launch of its own; 65 us
+// latency (32k: 7.6 us, and 63 us for Q in a launch of its own; 62 to 65 us
 // together).  Giving the top-k launch a share as well was slower: its 1024
 // threads and 50 KB of LDS leave one quantizing workgroup per CU, whose waves
 // all load and then all compute (8k prefill 522 us with every block here, 545
