@@ -42,6 +42,17 @@
 //   1280     8     32.8   33.6     34.3     73.8
 //   2048    16     52.3   54.7     54.6      161
 //   2048    32     91.4   96.1     82.3      246
+//   per-query window, nine tenths of the prompt
+//   1152     9     38.4   38.2     33.5
+//   1344     7     37.8   39.5     35.5            (last workgroups not full)
+//   2016    14     63.6   65.6     66.2            (FP8, 288 kFull workgroups)
+//   per-query window, all of the prompt
+//    512     2     13.4   14.3     14.6            (4 units a head)
+//   1152     9     37.4   40.1     33.0
+//   1440    18     65.9   70.4     51.0
+//   1536    48      163    171      114
+//   2016    14     54.9   58.0     59.1
+//   2016    18     67.1   71.1     66.8
 //   nothing quantized
 //    256     4     16.7   14.2     15.8     14.4
 //    320     4     17.0   14.5     16.0     20.1
@@ -68,10 +79,12 @@
 // more where the last workgroup of a head is not full); the key-list stage of
 // full-precision keys leaves them nothing to cover, so where that is most of
 // the work kFull is at least as good, unless its workgroups (8 units each, the
-// last of a head not full) are more than the CUs (2044 units of 73 heads, 7
-// tiles: kFull 51.3, kHalf 36.0).  With a per-query window the smaller
-// workgroups also list fewer keys (1536 units, 3 tiles, FP4: kFull 32.1, kHalf
-// 27.4; 516 units, 6 tiles: kHalf 33.4, kSplit2 30.4).
+// last of a head not full) are more than the CUs and the scan is short (2044
+// units of 73 heads, 7 tiles: kFull 51.3, kHalf 36.0; 2016 of 72, 14 tiles:
+// 43.3, 48.1).  With a per-query window the smaller workgroups also list fewer
+// keys (1536 units, 3 tiles, FP4: kFull 32.1, kHalf 27.4; 516 units, 6 tiles:
+// kHalf 33.4, kSplit2 30.4), the less so the more of the prompt the window is;
+// a window of all of it is one more scan of listed keys.
 #pragma once
 
 #include <cstdint>
@@ -94,8 +107,9 @@ struct AttnShape {
 
 // How the keys of a row are read: coded for the most part, all of them as
 // dense rows, a mixed or a mostly listed (full-precision) scan, or a per-query
-// window, whose key list grows with the rows of a workgroup.
-enum class AttnKeys { kCoded, kDense, kMixed, kListed, kBanded };
+// window, whose key list grows with the rows of a workgroup until the window
+// is most of the prompt, or all of it.
+enum class AttnKeys { kCoded, kDense, kMixed, kListed, kBanded, kBandedWide, kBandedAll };
 
 // `full` of the L keys of the last row are vertical lines or in its window;
 // dense = nothing is quantized, band = the window is per query.  kHalf against
@@ -104,7 +118,9 @@ enum class AttnKeys { kCoded, kDense, kMixed, kListed, kBanded };
 // to 1.09 at 0.9.
 inline AttnKeys attn_keys(int64_t full, int64_t L, bool dense, bool band) {
   if (dense) return AttnKeys::kDense;
-  if (band) return AttnKeys::kBanded;
+  if (band)
+    return 100 * full >= 97 * L ? AttnKeys::kBandedAll
+           : 4 * full >= 3 * L ? AttnKeys::kBandedWide : AttnKeys::kBanded;
   return 50 * full >= 31 * L ? AttnKeys::kListed
          : 5 * full >= 2 * L ? AttnKeys::kMixed : AttnKeys::kCoded;
 }
@@ -117,13 +133,16 @@ inline AttnShape choose_attn_shape(int64_t units, int64_t heads, int64_t tiles, 
     int64_t once, half_more, twice;   // kSplit2, see above
     int64_t half_many;                // kHalf takes more workgroups than CUs
   };
-  constexpr int64_t kNever = (int64_t)1 << 40, kSplit8Twice = 16, kDenseSplit8 = 12;
+  constexpr int64_t kNever = (int64_t)1 << 40, kSplit8Twice = 16, kDenseSplit8 = 12,
+                    kSecondTurn = 12;
   static constexpr Lines kLines[] = {
       {12, 96, 128, 3},        // kCoded
       {8, 12, 24, 4},          // kDense
       {12, 24, 48, 3},         // kMixed
       {5, 20, 32, kNever},     // kListed
       {5, 96, 128, 0},         // kBanded
+      {5, 9, 14, 0},           // kBandedWide
+      {5, 9, 18, kNever},      // kBandedAll
   };
   const Lines& t = kLines[(int)keys];
   const int64_t n4 = (units + 3) / 4, n8 = (units + 7) / 8;
@@ -134,7 +153,12 @@ inline AttnShape choose_attn_shape(int64_t units, int64_t heads, int64_t tiles, 
   if ((wg4 <= n_cu && tiles >= t.once) || (2 * wg4 <= 3 * n_cu && tiles >= t.half_more) ||
       (wg4 <= 2 * n_cu && tiles >= t.twice))
     return {AttnKind::kSplit2, wg4, 0};
-  if (wg4 <= n_cu || (wg4 <= 2 * n_cu && (tiles >= t.half_many + (units % 4 != 0) || n8 * heads > n_cu)))
+  // Whether kHalf's workgroups cover each other's waits.  Where not, they must
+  // spread a head over more CUs, or spare kFull a second turn of short scans.
+  const bool covers = t.half_many != kNever;
+  if (wg4 <= n_cu ? covers || n4 > n8
+                  : wg4 <= 2 * n_cu && (tiles >= t.half_many + (units % 4 != 0) ||
+                                        (n8 * heads > n_cu && (covers || tiles < kSecondTurn))))
     return {AttnKind::kHalf, wg4, (int)(n_cu / heads)};
   return {AttnKind::kFull, n8 * heads, 0};
 }

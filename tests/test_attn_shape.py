@@ -15,9 +15,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2608_27875_amd", "csrc")
 FULL, HALF, SPLIT2, SPLIT8 = range(4)
 UNITS = {FULL: 8, HALF: 4, SPLIT2: 4, SPLIT8: 1}   # per workgroup
-CODED, DENSE, MIXED, LISTED, BANDED = range(5)
-SHARE = {CODED: 0.05, DENSE: 1.0, MIXED: 0.5, LISTED: 1.0, BANDED: 0.5}
-MODE = {CODED: 0, DENSE: 1, MIXED: 0, LISTED: 0, BANDED: 2}
+CODED, DENSE, MIXED, LISTED, BANDED, WIDE, WHOLE = range(7)   # the last three: per-query windows
+SHARE = {CODED: 0.05, DENSE: 1.0, MIXED: 0.5, LISTED: 1.0, BANDED: 0.5, WIDE: 0.9, WHOLE: 1.0}
+MODE = {CODED: 0, DENSE: 1, MIXED: 0, LISTED: 0, BANDED: 2, WIDE: 2, WHOLE: 2}
 
 
 @pytest.fixture(scope="module")
@@ -39,7 +39,7 @@ def test_every_unit_has_one_workgroup(choose):
     cases = [(g * -(-L // 32), heads, L, int(share * L), mode, n_cu)
              for g in (1, 4, 5, 8) for heads in (1, 2, 8, 40, 300)
              for L in (1, 33, 500, 2000, 9000, 131072) for share, mode in
-             ((0.02, 0), (0.5, 0), (1.0, 0), (1.0, 1), (0.5, 2)) for n_cu in (80, 256)]
+             ((0.02, 0), (0.5, 0), (1.0, 0), (1.0, 1), (0.5, 2), (0.9, 2), (1.0, 2)) for n_cu in (80, 256)]
     for (units, heads, L, full, mode, n_cu), (kind, grid, fold, _) in zip(cases, choose(cases)):
         assert grid % heads == 0
         n = grid // heads   # workgroups per KV head
@@ -51,9 +51,10 @@ def test_every_unit_has_one_workgroup(choose):
 
 def test_key_classes(choose):
     cases = [(1, 1, 1000, full, mode, 256) for full, mode in
-             ((0, 0), (399, 0), (400, 0), (619, 0), (620, 0), (1000, 0), (0, 1), (1000, 1), (900, 2))]
-    assert [c[3] for c in choose(cases)] == [CODED, CODED, MIXED, MIXED, LISTED, LISTED, DENSE,
-                                             DENSE, BANDED]
+             ((0, 0), (399, 0), (400, 0), (619, 0), (620, 0), (1000, 0), (0, 1), (1000, 1),
+              (0, 2), (749, 2), (750, 2), (969, 2), (970, 2))]
+    assert [c[3] for c in choose(cases)] == [CODED, CODED, MIXED, MIXED, LISTED, LISTED, DENSE, DENSE,
+                                             BANDED, BANDED, WIDE, WIDE, WHOLE]
 
 
 def test_lines(choose):
@@ -80,7 +81,17 @@ def test_lines(choose):
             ((257, 1, 8, DENSE), SPLIT2), ((192, 8, 11, DENSE), HALF), ((192, 8, 12, DENSE), SPLIT2),
             ((256, 8, 23, DENSE), HALF), ((256, 8, 24, DENSE), SPLIT2), ((257, 8, 200, DENSE), FULL),
             ((129, 8, 1, BANDED), HALF), ((257, 1, 4, BANDED), HALF),
-            ((257, 1, 5, BANDED), SPLIT2), ((192, 8, 95, BANDED), HALF), ((192, 8, 96, BANDED), SPLIT2)]
+            ((257, 1, 5, BANDED), SPLIT2), ((192, 8, 95, BANDED), HALF), ((192, 8, 96, BANDED), SPLIT2),
+            # full-precision lists: a second turn of kFull's workgroups, half workgroups that
+            # spread no head further
+            ((28, 73, 11, LISTED), HALF), ((28, 73, 12, LISTED), FULL), ((4, 128, 2, LISTED), FULL),
+            ((5, 128, 2, LISTED), HALF), ((4, 128, 2, MIXED), HALF),
+            ((128, 8, 4, WIDE), HALF), ((128, 8, 5, WIDE), SPLIT2), ((192, 8, 8, WIDE), HALF),
+            ((192, 8, 9, WIDE), SPLIT2), ((256, 8, 13, WIDE), HALF), ((256, 8, 14, WIDE), SPLIT2),
+            ((257, 8, 14, WIDE), FULL),
+            ((4, 128, 2, WHOLE), FULL), ((128, 8, 4, WHOLE), HALF), ((128, 8, 5, WHOLE), SPLIT2),
+            ((192, 8, 8, WHOLE), FULL), ((192, 8, 9, WHOLE), SPLIT2), ((256, 8, 17, WHOLE), FULL),
+            ((256, 8, 18, WHOLE), SPLIT2), ((28, 73, 11, WHOLE), HALF), ((28, 73, 12, WHOLE), FULL)]
     got = choose([(u, heads, 64 * t, int(64 * t * SHARE[keys]), MODE[keys], 256)
                   for (u, heads, t, keys), _ in want])
     assert [(k, c[0]) for (k, _), c in zip(want, got)] == want
